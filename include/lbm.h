@@ -330,7 +330,7 @@ lbm_status lbm_get_launch(const lbm_lattice *L, int *block_x, int *nodes_per_thr
 
 /* Steps per pass over HBM.  steps_per_pass = 2 (temporal blocking): lbm_step
  * advances pairs of steps with one kernel in which a workgroup streams a
- * tile of 64 x BY nodes (by default BY = 13 for FP32 and FP16, 5 for FP64) through
+ * tile of 64 x BY nodes (by default BY = 13 for FP32 and FP16, 7 for FP64) through
  * ranges of z_planes planes, computes the first step on the tile plus a
  * one-node halo into LDS and the second from LDS into HBM.  Per pair of
  * steps every node's populations are read about once (the halo rows are
@@ -347,7 +347,7 @@ lbm_status lbm_get_launch(const lbm_lattice *L, int *block_x, int *nodes_per_thr
  * the form's default; 5, five-row tiles (two workgroups per compute unit);
  * 12, twelve-row tiles (15 waves, three of step 2's 12 on each SIMD;
  * measured faster than 13 rows on 512 x 256 x 256 FP32, slower on
- * 1024 x 512 x 512); FP64 tiles have five rows either way.  Every variant
+ * 1024 x 512 x 512); FP64 tiles have seven rows either way.  Every variant
  * gives the same bits.  steps_per_pass = 1: one single sweep per step (the
  * default).  Errors: LBM_ERR_ARG (NULL, steps_per_pass not 1 or 2,
  * z_planes < 0, tile_rows not 0, 5 or 12). */
@@ -366,7 +366,7 @@ lbm_status lbm_get_step(const lbm_lattice *L, unsigned long long *steps);
  * placement) one untimed and trial_steps >= 1 timed steps, and, in the
  * row-major layout without those options, for each two-step pass
  * (lbm_set_steps_per_pass: z ranges of 16, 32 or 64 planes, tiles of the
- * form's default rows, 5 or 12 rows (FP64: its 5 only), slab or
+ * form's default rows, 5 or 12 rows (FP64: its 7 only), slab or
  * dispatch-order placement) one
  * untimed and trial_steps timed pairs, on the lattice's stream (HIP events,
  * compared per step).  The steps are part of the run (results do not depend
@@ -538,7 +538,7 @@ lbm_status lbm_batch_get_shape(const lbm_batch *B, int *block_x, int *tile_nodes
  * at a time as lbm_set_steps_per_pass does for one lattice):
  *   1 (the default)  one step per launch;
  *   2                every chunk by passes of two steps: one launch per
- *                    storage form over the 64 x 13 (FP64: 64 x 5) tiles and
+ *                    storage form over the 64 x 13 (FP64: 64 x 7) tiles and
  *                    z ranges of z_planes planes (0: 32) of all its jobs, or
  *                    the single-lattice two-step kernel for a chunk of one
  *                    job; every job is then stored row-major with padded

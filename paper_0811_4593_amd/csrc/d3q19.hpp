@@ -192,11 +192,11 @@ __device__ __forceinline__ void face_rule(T (&d)[19], bool pressure, T keep_n, T
   }
 }
 
-// Edge (two bits of m) or corner (three bits), no-slip; the density of a
-// bordering pressure face (pmask: the pressure faces among m's faces; at
-// most one, as pressure faces lie on one axis) when there is one.
+// Edge (two bits of m) or corner (three bits), no-slip; r0: the density of a
+// bordering pressure face when there is one (pressure; at most one, as
+// pressure faces lie on one axis).
 template <class T>
-__device__ __forceinline__ void edge_corner_rule(T (&d)[19], unsigned m, const NodeParams<T> &p, unsigned pmask) {
+__device__ __forceinline__ void edge_corner_rule(T (&d)[19], unsigned m, bool pressure, T r0) {
   unsigned U = 0;
 #pragma unroll
   for (int b = 0; b < 6; ++b)
@@ -206,11 +206,6 @@ __device__ __forceinline__ void edge_corner_rule(T (&d)[19], unsigned m, const N
   const int sy = int((m >> 2) & 1u) - int((m >> 3) & 1u);
   const int sz = int((m >> 4) & 1u) - int((m >> 5) & 1u);
   const int nb = __popc(m);
-  const unsigned pm = m & pmask;
-  T r0 = T(1);
-#pragma unroll
-  for (int b = 0; b < 6; ++b)
-    if (pm & (1u << b)) r0 = p.rho_p[b];
   const int ex = (nb == 2 && sx == 0) ? 1 : 0;
   const int ey = (nb == 2 && sy == 0) ? 1 : 0;
   const int ez = (nb == 2 && sz == 0) ? 1 : 0;
@@ -230,10 +225,20 @@ __device__ __forceinline__ void edge_corner_rule(T (&d)[19], unsigned m, const N
   for (int k = 0; k < 18; ++k) s += ((bur >> k) & 1u) ? T(0) : d[k];
   const T db_v = s / (nb == 2 ? T(22) : T(18));
   const T db_p = (r0 - T(1) - s) / (nb == 2 ? T(14) : T(18));
-  const T db = pm ? db_p : db_v;
+  const T db = pressure ? db_p : db_v;
 #pragma unroll
   for (int k = 0; k < 18; ++k) d[k] = ((bur >> k) & 1u) ? db : d[k];
   d[18] = T(12) * db;
+}
+
+// Density of the pressure face among the faces pm (at most one bit).
+template <class T>
+__device__ __forceinline__ T edge_density(unsigned pm, const T (&rho_p)[6]) {
+  T r0 = T(1);
+#pragma unroll
+  for (int b = 0; b < 6; ++b)
+    if (pm & (1u << b)) r0 = rho_p[b];
+  return r0;
 }
 
 // Boundary rule of a node with face mask m and given face values (a
@@ -252,7 +257,7 @@ __device__ __forceinline__ void boundary_rule(T (&d)[19], unsigned m, const Node
   if (m == 8u) face_rule<T, 3>(d, (pmask & 8u) != 0u, keep_n, vx, vy, vz, r0);
   if (m == 16u) face_rule<T, 4>(d, (pmask & 16u) != 0u, keep_n, vx, vy, vz, r0);
   if (m == 32u) face_rule<T, 5>(d, (pmask & 32u) != 0u, keep_n, vx, vy, vz, r0);
-  if (m & (m - 1u)) edge_corner_rule<T>(d, m, p, pmask);
+  if (m & (m - 1u)) edge_corner_rule<T>(d, m, (m & pmask) != 0u, edge_density<T>(m & pmask, p.rho_p));
 }
 
 // Boundary rule of a node of a box whose faces take the lattice's face
@@ -272,7 +277,35 @@ __device__ __forceinline__ void box_boundary_rule(T (&d)[19], unsigned m, const 
   LBM_FACE(4)
   LBM_FACE(5)
 #undef LBM_FACE
-  if (m & (m - 1u)) edge_corner_rule<T>(d, m, p, p.p_mask);
+  if (m & (m - 1u)) edge_corner_rule<T>(d, m, (m & p.p_mask) != 0u, edge_density<T>(m & p.p_mask, p.rho_p));
+}
+
+// As box_boundary_rule, with the face values in a table in LDS, tab[b] =
+// (velocity, density) of face b: a kernel that runs the rule inside a loop
+// keeps no scalar registers for the 24 values (the compiler otherwise holds
+// them across the loop and spills).
+template <class T>
+__device__ __forceinline__ void box_boundary_rule_table(T (&d)[19], unsigned m, unsigned p_mask, unsigned rule_flags,
+                                                        const T (*tab)[4]) {
+  const T keep_n = (rule_flags & kRuleNoTransverse) ? T(0) : T(1);
+#define LBM_FACE(b)              \
+  if (m == (1u << (b)))          \
+    face_rule<T, b>(d, ((p_mask >> (b)) & 1u) != 0u, keep_n, tab[b][0], tab[b][1], tab[b][2], tab[b][3]);
+  LBM_FACE(0)
+  LBM_FACE(1)
+  LBM_FACE(2)
+  LBM_FACE(3)
+  LBM_FACE(4)
+  LBM_FACE(5)
+#undef LBM_FACE
+  if (m & (m - 1u)) {
+    const unsigned pm = m & p_mask;
+    T r0 = T(1);
+#pragma unroll
+    for (int b = 0; b < 6; ++b)
+      if (pm & (1u << b)) r0 = tab[b][3];
+    edge_corner_rule<T>(d, m, pm != 0u, r0);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -349,8 +382,23 @@ __device__ __forceinline__ void general_wall_rule(T (&d)[19], unsigned U) {
 //   d_k <- d_k + omega (d_k^eq - d_k), omega = 1/tau, c_s^2 = 1/3.
 // A body force F enters as the velocity shift tau F / rho inside f^eq
 // (eq_gravity): u = (sum d c + tau F) / rho.
+//
+// Every multiply-add is written out (fused_add) and the compiler's own
+// contraction is off: which products it fuses depends on the code around the
+// call, and every kernel that advances a lattice has to give the same bits.
+__device__ __forceinline__ double fused_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fused_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// c_k . u of a diagonal link is one component's momentum times 1 / rho fused
+// with the other component's velocity; whether the first component is the
+// fused one.
+__host__ __device__ constexpr bool fuses_first(int k) {
+  return cx(k) ? (cx(k) < 0 && cy(k) + cz(k) < 0) : !(cy(k) < 0 && cz(k) > 0);
+}
+
 template <class T>
 __device__ __forceinline__ void bgk_collide(T (&d)[19], T omega, const T (&tau_f)[3]) {
+#pragma clang fp contract(off)
   // Moments: partial sums over the populations with c_a = +1, -1 (and, for
   // x, 0); each starts from its first term (0 + x is not foldable under
   // signed zeros, so a zero start would cost an instruction).
@@ -379,24 +427,26 @@ __device__ __forceinline__ void bgk_collide(T (&d)[19], T omega, const T (&tau_f
     ir = __builtin_amdgcn_rcpf(rho);
   else
     ir = T(1) / rho;
-  const T ux = (xp - xm + tau_f[0]) * ir, uy = (yp - ym + tau_f[1]) * ir, uz = (zp - zm + tau_f[2]) * ir;
+  const T j[3] = {xp - xm + tau_f[0], yp - ym + tau_f[1], zp - zm + tau_f[2]};
+  const T u[3] = {j[0] * ir, j[1] * ir, j[2] * ir};
   // d_eq = w (drho + rho (3 cu + 4.5 cu^2 - 1.5 u^2)) = w (C + cu (B + A cu)), and
   // d + omega (d_eq - d) = (1 - omega) d + (omega w) (C + cu (B + A cu)).
   const T A = T(4.5) * rho, B = T(3) * rho;
-  const T C = drho - T(1.5) * rho * (ux * ux + uy * uy + uz * uz);
+  const T C = fused_add(-(T(1.5) * rho), fused_add(u[2], u[2], fused_add(u[0], u[0], u[1] * u[1])), drho);
   const T keep = T(1) - omega;
 #pragma unroll
   for (int k = 0; k < 19; ++k) {
     const T ow = omega * weight<T>(k);
     T t = C;
     if (k != 18) {
-      // c.u from the non-zero components only
-      T cu = cx(k) ? T(cx(k)) * ux : T(cy(k)) * uy;
-      if (cx(k) && cy(k)) cu += T(cy(k)) * uy;
-      if (cz(k)) cu = (cx(k) || cy(k)) ? cu + T(cz(k)) * uz : T(cz(k)) * uz;
-      t = (A * cu + B) * cu + C;
+      const int c[3] = {cx(k), cy(k), cz(k)};
+      const int a = c[0] ? 0 : (c[1] ? 1 : 2);  // first moving component, and the second if there is one
+      const int b = a == 0 ? (c[1] ? 1 : 2) : 2;
+      T cu = T(c[a]) * u[a];
+      if (b != a && c[b]) cu = fuses_first(k) ? fused_add(T(c[a]) * j[a], ir, T(c[b]) * u[b]) : fused_add(T(c[b]) * j[b], ir, cu);
+      t = fused_add(fused_add(A, cu, B), cu, C);
     }
-    d[k] = keep * d[k] + ow * t;
+    d[k] = fused_add(keep, d[k], ow * t);
   }
 }
 

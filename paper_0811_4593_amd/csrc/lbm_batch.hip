@@ -298,7 +298,7 @@ struct BatchBox {
 // buffer, so that each lattice gets the bits of two single sweeps.  remap:
 // the box list's order on the XCDs (logical_block).
 template <class F, int BYI>
-__global__ __launch_bounds__(64 * (BYI + 3)) void batch_pass_kernel(const BatchLat *__restrict__ lats,
+__global__ __launch_bounds__((Sweep2Tile<F, BYI>::kThreads), (Sweep2Tile<F, BYI>::kWaves)) void batch_pass_kernel(const BatchLat *__restrict__ lats,
                                                                     const BatchBox *__restrict__ boxes,
                                                                     const int *__restrict__ nboxes, int s, int parity,
                                                                     int zc, int remap) {
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(64 * (BYI + 3)) void batch_pass_kernel(const BatchL
   // global (not flat) accesses: the addresses come from memory
   const global_ptr<const S> src = (global_ptr<const S>)(L.buf[parity]);
   const global_ptr<S> dst = (global_ptr<S>)(L.buf[parity ^ 1]);
-  sweep2_box<F, BYI, global_ptr<const S>, global_ptr<S>>(src, dst, a, bx.tx, bx.ty, bx.tz, ring);
+  sweep2_box<F, BYI>(src, dst, a, bx.tx, bx.ty, bx.tz, ring);
 }
 
 // own: the grid is the tile table's capacity, one workgroup per entry.

@@ -28,7 +28,7 @@
 namespace lbm {
 
 template <class F, int BYI>
-__global__ __launch_bounds__(64 * (BYI + 3)) void sweep2_kernel(
+__global__ __launch_bounds__((Sweep2Tile<F, BYI>::kThreads), (Sweep2Tile<F, BYI>::kWaves)) void sweep2_kernel(
     const typename F::S *__restrict__ src, typename F::S *__restrict__ dst,
     Sweep2Args<typename Codec<typename F::S>::T> a) {
   using S = typename F::S;
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(64 * (BYI + 3)) void sweep2_kernel(
   const unsigned b = logical_block(blockIdx.x, gridDim.x, a.xcd_remap, 1u);
   const unsigned tx = b % unsigned(a.tiles_x), rest = b / unsigned(a.tiles_x);
   const unsigned ty = rest % unsigned(a.tiles_y), tz = rest / unsigned(a.tiles_y);
-  sweep2_box<F, BYI, const S *__restrict__, S *__restrict__>(src, dst, a, tx, ty, tz, ring);
+  sweep2_box<F, BYI>((global_ptr<const S>)src, (global_ptr<S>)dst, a, tx, ty, tz, ring);
 }
 
 template <class F, int BYI>
@@ -71,9 +71,13 @@ static hipError_t launch_sweep2_t(const SweepConfig &c, int zc, const void *src,
   return hipGetLastError();
 }
 
+bool sweep2_takes(const PopLayout &lay, int storage) {
+  const size_t esize = storage == kStoreF64 ? 8 : (storage == kStoreF32 ? 4 : 2);
+  return lay.row_stride == 19 * lay.pop_stride && lay.row_stride * esize < (size_t(1) << 32);
+}
+
 hipError_t launch_sweep2(const SweepConfig &c, int zc, int rows, const void *src, void *dst, hipStream_t s) {
-  // row-major layout only: the tile's rows are whole rows of one population
-  if (c.layout.row_stride != 19 * c.layout.pop_stride || zc < 1) return hipErrorInvalidValue;
+  if (!sweep2_takes(c.layout, c.storage) || zc < 1) return hipErrorInvalidValue;
   switch (c.storage) {
     case kStoreF64: return launch_sweep2_t<FormF64, Sweep2Rows<FormF64>::kBYI>(c, zc, src, dst, s);
     case kStoreF32:

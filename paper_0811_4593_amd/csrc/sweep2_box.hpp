@@ -22,18 +22,26 @@
 
 namespace lbm {
 
-// Step 2 at plane z pulls population k from plane z - cz(k) of step 1.  A
-// step-1 plane's populations with cz = -1 are read by step 2 in the same
-// round, those with cz = 0 one round later and those with cz = +1 two
-// rounds later: rings of 1, 2 and 3 planes, 38 population planes in all.
+// The thread that computes step 1 of the node (x, y) also computes its step
+// 2, so the three populations that move along z or not at all (cx = cy = 0)
+// stay in its registers.  The 16 others pass through LDS: step 2 at plane z
+// pulls population k from plane z - cz(k) of step 1, so a step-1 plane's
+// populations with cz = -1 are read by step 2 in the same round, those with
+// cz = 0 one round later and those with cz = +1 two rounds later: rings of
+// 1, 2 and 3 slots, 4 + 2 * 8 + 3 * 4 = 32 population planes in all.
+__host__ __device__ constexpr bool own_column(int k) { return cx(k) == 0 && cy(k) == 0; }
 __host__ __device__ constexpr int ring_depth(int k) { return cz(k) < 0 ? 1 : (cz(k) == 0 ? 2 : 3); }
-__host__ __device__ constexpr int ring_base(int k) {
-  int b = 0;
-  for (int j = 0; j < k; ++j) b += ring_depth(j);
-  return b;
+// Rank of population k among those of its cz that pass through LDS.
+__host__ __device__ constexpr int ring_rank(int k) {
+  int r = 0;
+  for (int j = 0; j < k; ++j) r += (!own_column(j) && cz(j) == cz(k)) ? 1 : 0;
+  return r;
 }
-constexpr int kRingPlanes = ring_base(19);
-static_assert(kRingPlanes == 38, "5 + 2 * 9 + 3 * 5 population planes");
+// First plane of each ring, and planes of one of its slots.
+__host__ __device__ constexpr int ring_first(int c) { return c < 0 ? 0 : (c == 0 ? 4 : 20); }
+__host__ __device__ constexpr int ring_slot_planes(int c) { return c == 0 ? 8 : 4; }
+constexpr int kRingPlanes = 32;
+static_assert(ring_rank(17) == 3 && ring_rank(11) == 7 && ring_rank(16) == 3, "4, 8 and 4 populations per slot");
 
 template <class T>
 struct Sweep2Args {
@@ -57,198 +65,212 @@ __device__ __forceinline__ unsigned box_faces(unsigned bc_mask, int x, int y, in
   return m;
 }
 
-// Boundary rule and collision of one node (the plain path of update_node).
-template <class T>
-__device__ __forceinline__ void rule_and_collide(T (&f)[19], unsigned m, const NodeParams<T> &p) {
-  if (m) box_boundary_rule<T>(f, m, p);
-  bgk_collide<T>(f, p.omega, p.tau_f);
-}
-
 template <class F, int BYI>
 struct Sweep2Tile {
   static constexpr int kHX = 66;                 // 64 interior columns + halo
   static constexpr int kHY = BYI + 2;            // BYI interior rows + halo
   static constexpr int kPlane = kHX * kHY;       // elements of one population plane
   static constexpr int kThreads = 64 * (BYI + 3);  // a wave per halo row and one for the halo columns
+  // Waves per SIMD the register allocation has to leave room for: one
+  // workgroup per compute unit, two of the small tiles (8 waves).
+  static constexpr int kWaves = BYI <= 5 ? 4 : (BYI + 3 + 3) / 4;
 };
 
-// Step 1 of the node (x, y, z) (wrapped lattice coordinates): pull from HBM,
-// rule, collision, rounding with the first step's key; the encoded result
-// goes to LDS cell `cell` of the ring planes of round p.  SrcP: a pointer to
-// const S (a global-address-space pointer where the address comes from
-// memory, so that the loads are global rather than flat).
-// ps, rs: the lattice's population and row strides (a.pop_stride,
-// a.row_stride), passed separately (see sweep2_box).
-// ROWS: y is uniform over the wave, so each source row is read through a
-// descriptor of its own (base at the row's start, the lane's byte offset and
-// the population's start as scalar offset) rather than through 64-bit
-// vector addresses.
-template <class F, bool ROWS, class SrcP>
-__device__ __forceinline__ void step1_node(SrcP src, typename F::S *ring, int plane_elems,
-                                           const Sweep2Args<typename Codec<typename F::S>::T> &a, int x, int y, int z,
-                                           int cell, int p, size_t ps, size_t rs) {
-  using S = typename F::S;
-  using T = typename Codec<S>::T;
-  const unsigned nx = unsigned(a.nx), ny = unsigned(a.ny), nz = unsigned(a.nz);
-  const unsigned ym = y == 0 ? ny - 1 : unsigned(y) - 1, yp = unsigned(y) == ny - 1 ? 0 : unsigned(y) + 1;
-  const unsigned zm = z == 0 ? nz - 1 : unsigned(z) - 1, zp = unsigned(z) == nz - 1 ? 0 : unsigned(z) + 1;
-  const unsigned xm = x == 0 ? nx - 1 : unsigned(x) - 1, xp = unsigned(x) == nx - 1 ? 0 : unsigned(x) + 1;
-  const unsigned yy[3] = {yp, unsigned(y), ym};
-  const unsigned zz[3] = {zp, unsigned(z), zm};
-  const unsigned xs[3] = {xp, unsigned(x), xm};
-  T f[19];
-  if constexpr (ROWS) {
-    // (read through readfirstlane: the compiler cannot see that the values
-    // passed through the register barriers are uniform, and a descriptor it
-    // takes for divergent would be built lane by lane in a loop)
-    const unsigned yu = __builtin_amdgcn_readfirstlane(unsigned(y)), zu = __builtin_amdgcn_readfirstlane(unsigned(z));
-    const unsigned rsu = __builtin_amdgcn_readfirstlane(unsigned(rs));
-    const unsigned pb = __builtin_amdgcn_readfirstlane(unsigned(ps)) * unsigned(sizeof(S)), rb = rsu * unsigned(sizeof(S));
-    const unsigned yr[3] = {yu == ny - 1 ? 0 : yu + 1, yu, yu == 0 ? ny - 1 : yu - 1};
-    const unsigned zr[3] = {zu == nz - 1 ? 0 : zu + 1, zu, zu == 0 ? nz - 1 : zu - 1};
-    const unsigned xo[3] = {xp * unsigned(sizeof(S)), unsigned(x) * unsigned(sizeof(S)), xm * unsigned(sizeof(S))};
-    S raw[19];
-#pragma unroll
-    for (int k = 0; k < 19; ++k) {
-      const size_t row = size_t(yr[cy(k) + 1] + ny * zr[cz(k) + 1]) * rsu;
-      raw[k] = buf_load<S>(raw_buffer((const S *)src + row, rb), xo[cx(k) + 1], unsigned(k) * pb);
-    }
-    // All 19 loads in flight before the first is used: without this
-    // statement the compiler, short of registers, waited for each load
-    // before issuing the next.
-    asm volatile(""
-                 : "+v"(raw[0]), "+v"(raw[1]), "+v"(raw[2]), "+v"(raw[3]), "+v"(raw[4]), "+v"(raw[5]), "+v"(raw[6]),
-                   "+v"(raw[7]), "+v"(raw[8]), "+v"(raw[9]), "+v"(raw[10]), "+v"(raw[11]), "+v"(raw[12]),
-                   "+v"(raw[13]), "+v"(raw[14]), "+v"(raw[15]), "+v"(raw[16]), "+v"(raw[17]), "+v"(raw[18]));
-#pragma unroll
-    for (int k = 0; k < 19; ++k) f[k] = Codec<S>::decode(raw[k]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 19; ++k) {
-      const size_t row = size_t(yy[cy(k) + 1] + ny * zz[cz(k) + 1]) * rs;
-      f[k] = Codec<S>::decode(src[size_t(k) * ps + row + xs[cx(k) + 1]]);
-    }
-  }
-  rule_and_collide<T>(f, box_faces(a.p.bc_mask, x, y, z, a.nx, a.ny, a.nz), a.p);
-  const unsigned n = (unsigned(z) * ny + unsigned(y)) * nx + unsigned(x);
-  const unsigned r0 = F::kStochastic ? fmix32(n * 0x9e3779b1u + a.key0) : 0u;
-  const int s2 = p & 1, s3 = p % 3;
-#pragma unroll
-  for (int k = 0; k < 19; ++k) {
-    const int slot = ring_depth(k) == 1 ? 0 : (ring_depth(k) == 2 ? s2 : s3);
-    ring[(ring_base(k) + slot) * plane_elems + cell] = encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
-  }
+// Fix the point in the program where a node's 19 values are complete: values
+// from memory have been waited for, computed ones are in registers, and
+// nothing on them moves across.
+template <class V>
+__device__ __forceinline__ void complete(V (&v)[19]) {
+  asm volatile(""
+               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
+                 "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15]),
+                 "+v"(v[16]), "+v"(v[17]), "+v"(v[18]));
 }
 
 // The two steps of one workgroup's box: tile (tx, ty) of 64 x BYI nodes and
 // z range tz of a.zc planes, with the population ring `ring` in LDS
 // (kRingPlanes * Sweep2Tile<F, BYI>::kPlane elements).  Every thread of the
-// workgroup calls it (it holds barriers).  SrcP, DstP: pointers to const S
-// and to S that do not alias (plain pointers from kernel arguments, or
-// global-address-space pointers).
-template <class F, int BYI, class SrcP, class DstP>
-__device__ __forceinline__ void sweep2_box(SrcP src, DstP dst,
+// workgroup calls it (it holds barriers).
+//
+// Waves 0..BYI+1 each own a row of the tile and its halo, 64 columns; the
+// last wave owns the halo columns left and right of every row.  A round
+// (one z plane) of a wave: take the 19 loaded sources of its node, issue the
+// loads of the next plane's, compute step 1 and write it to the ring;
+// barrier; step 2 of its node one plane behind from the ring and its own
+// registers; wait for the loads; store; barrier.  The loads so have the
+// whole round to arrive, beneath both steps' arithmetic, and the wait, placed
+// before the stores, never waits for a store (loads and stores share one
+// counter that drains in order).  With one workgroup per compute unit a pass
+// that loads, waits, computes and stores in turn leaves memory idle through
+// the arithmetic and the other way round: without any arithmetic it still
+// took 8.9 ms on the 1024 x 512 x 512 FP32 duct, with it 11.1 ms, this way
+// 8.5 ms (9.6 TB/s at the algorithmic 152 B per update).  512 x 256 x 256
+// FP64: 2.87 ms, 2.19 ms with the loads ahead and 7 rows (5 rows 2.38 ms, 6
+// rows 2.17-2.23 ms).
+template <class F, int BYI>
+__device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, global_ptr<typename F::S> dst,
                                            const Sweep2Args<typename Codec<typename F::S>::T> &a, unsigned tx,
                                            unsigned ty, unsigned tz, typename F::S *ring) {
   using S = typename F::S;
   using T = typename Codec<S>::T;
   using Tile = Sweep2Tile<F, BYI>;
   constexpr int HX = Tile::kHX, HY = Tile::kHY, PLANE = Tile::kPlane;
+  typedef global_ptr<const char> BytesIn;
+  __shared__ T faces[6][4];  // velocity and density of each face
+  if (threadIdx.x < 6u) {
+    const unsigned b = threadIdx.x;
+#pragma unroll
+    for (unsigned f = 0; f < 6u; ++f)
+      if (b == f) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) faces[f][d] = a.p.fv.v[f][d];
+        faces[f][3] = a.p.rho_p[f];
+      }
+  }
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int x0 = int(tx) * 64, y0 = int(ty) * BYI, zb = int(tz) * a.zc;
   const int ze = min(zb + a.zc, nz);
   const int w = min(64, nx - x0), hyc = min(BYI, ny - y0);  // interior columns and rows of this tile
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  const int lane0 = int(threadIdx.x) & 63;
-  // The FP32 form reads the step-1 sources of the halo rows and writes step
-  // 2 through per-row descriptors (no 64-bit vector address arithmetic:
-  // 0.3-2.4% faster on 1024 x 512 x 512 and 1.8% on 512 x 256 x 256, with
-  // 17% fewer vector instructions); the FP64 and FP16 forms, measured 2-5%
-  // slower so, keep the pointers.
-  constexpr bool kRowDescriptors = sizeof(S) == 4;
+  const int lane = int(threadIdx.x) & 63;
+  const bool columns = wave == HY;
+  // This lane's node: cell (hx, hy) of the tile with halo, lattice column x
+  // and row y (halo nodes wrapped, as the single sweep's pull reads them;
+  // idle lanes take a node of the tile).
+  const bool live1 = columns ? lane < 2 * (hyc + 2) : lane < w;
+  const int hy = columns ? min(lane >> 1, hyc + 1) : min(wave, hyc + 1);
+  const int hx = columns ? ((lane & 1) ? w + 1 : 0) : min(lane + 1, w);
+  int x = x0 + hx - 1, y = y0 + hy - 1;
+  x += x < 0 ? nx : (x >= nx ? -nx : 0);
+  y += y < 0 ? ny : (y >= ny ? -ny : 0);
+  const bool rows1 = columns || wave <= hyc + 1;              // the wave has step-1 nodes
+  const bool rows2 = !columns && wave >= 1 && wave <= hyc;  // and step-2 nodes
+  const unsigned mxy = box_faces(a.p.bc_mask & 15u, x, y, -1, nx, ny, nz);
+  const unsigned nxy = unsigned(y) * unsigned(nx) + unsigned(x);
+  const unsigned nplane = unsigned(nx) * unsigned(ny);
+  const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+  const int ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+  // lane byte offsets within a row, index c + 1 -> coordinate - c
+  const unsigned xo[3] = {unsigned(xp) * unsigned(sizeof(S)), unsigned(x) * unsigned(sizeof(S)),
+                          unsigned(xm) * unsigned(sizeof(S))};
+  const size_t pb = a.pop_stride * sizeof(S), rb = a.row_stride * sizeof(S), zbytes = rb * size_t(ny);
 
-  for (int p = 0, zz = zb - 1; zz <= ze; ++p, ++zz) {
-    // The lane index is passed through an empty asm statement each round, so
-    // that the compiler recomputes the per-lane addresses inside the loop
-    // instead of holding 2 x 19 of them in registers across it (they spilled
-    // to scratch).
-    int lane = lane0;
-    asm volatile("" : "+v"(lane));
-    // The strides likewise (FP32 and FP16 forms): the compiler then
-    // recomputes the 19 population offsets on the scalar unit each round
-    // instead of holding them across the loop in spilled scalar registers,
-    // which took a vector instruction per reload; 1024 x 512 x 512 FP32
-    // went from 6.19 to 5.76 ms per step.  (FP64, whose tiles hold 5 rows,
-    // ran 1.3% slower this way.)
-    size_t ps = a.pop_stride, rs = a.row_stride;
-    if constexpr (sizeof(S) < 8) asm volatile("" : "+s"(ps), "+s"(rs));
-    const int z1 = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
-    // Step 1 on the tile and its halo.  Waves 0..BYI+1 take the 64 interior
-    // columns of halo rows 0..BYI+1 (rows past the tile's last interior row
-    // + 1 idle); the last wave takes the left and right halo column of every
-    // row.  Halo cells hold the wrapped nodes, as the single sweep's pull
-    // reads them.
-    if (wave < HY) {
-      if (lane < w && wave <= hyc + 1) {
-        int y = y0 + wave - 1;
-        y += y < 0 ? ny : (y >= ny ? -ny : 0);
-        step1_node<F, kRowDescriptors, SrcP>(src, ring, PLANE, a, x0 + lane, y, z1, wave * HX + lane + 1, p, ps,
-                                             rs);
+  // Sources of the lane's node at plane z.  A row wave's rows are uniform:
+  // scalar bases plus the lane's x offset; the halo-column wave's differ by
+  // lane.
+  S raw[19];
+  auto load = [&](int z) {
+    const int zs[3] = {z == nz - 1 ? 0 : z + 1, z, z == 0 ? nz - 1 : z - 1};
+    if (!columns) {
+      const int yu[3] = {__builtin_amdgcn_readfirstlane(yp), __builtin_amdgcn_readfirstlane(y),
+                         __builtin_amdgcn_readfirstlane(ym)};
+#pragma unroll
+      for (int k = 0; k < 19; ++k) {
+        const S *row = (const S *)((const char *)(const S *)src + (size_t(zs[cz(k) + 1]) * zbytes + size_t(yu[cy(k) + 1]) * rb));
+        raw[k] = buf_load<S>(raw_buffer(row, unsigned(rb)), xo[cx(k) + 1], unsigned(k) * unsigned(pb));
       }
     } else {
-      const int hy = lane >> 1, right = lane & 1;
-      if (lane < 2 * HY && hy <= hyc + 1) {
-        int y = y0 + hy - 1;
-        y += y < 0 ? ny : (y >= ny ? -ny : 0);
-        int x = right ? x0 + w : x0 - 1;
-        x += x < 0 ? nx : (x >= nx ? -nx : 0);
-        step1_node<F, false, SrcP>(src, ring, PLANE, a, x, y, z1, hy * HX + (right ? w + 1 : 0), p, ps, rs);
+      const size_t yo[3] = {size_t(yp) * rb, size_t(y) * rb, size_t(ym) * rb};
+#pragma unroll
+      for (int k = 0; k < 19; ++k) {
+        const BytesIn plane = (BytesIn)src + (size_t(zs[cz(k) + 1]) * zbytes + size_t(k) * pb);
+        raw[k] = *(global_ptr<const S>)(plane + (yo[cy(k) + 1] + xo[cx(k) + 1]));
       }
     }
+  };
+
+  // LDS cells: `out` the lane's own cell, `in` the lowest cell step 2 reads.
+  S *const own = ring + hy * HX + hx;
+  const S *const low = own - HX - 1;
+  S e18 = S(0), e4 = S(0), e4_before = S(0), e5 = S(0);  // own column: rest, +z (one and two rounds back), -z
+  __syncthreads();  // the face table
+  load(zb == 0 ? nz - 1 : zb - 1);
+  complete(raw);
+  int s2 = 0, s3 = 0;  // ring slots of this round: p mod 2, p mod 3
+  for (int zz = zb - 1; zz <= ze; ++zz) {
+    const int z1 = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
+    const int s3_2 = s3 == 2 ? 0 : s3 + 1;  // slot of two rounds back (p - 2 = p + 1 mod 3)
+    T f[19];
+#pragma unroll
+    for (int k = 0; k < 19; ++k) f[k] = Codec<S>::decode(raw[k]);
+    complete(f);
+    load(zz == ze ? z1 : (z1 == nz - 1 ? 0 : z1 + 1));
+    S e18_now = S(0), e4_now = S(0);
+    if (rows1) {
+      const unsigned m = mxy | (z1 == 0 ? a.p.bc_mask & 16u : 0u) | (z1 == nz - 1 ? a.p.bc_mask & 32u : 0u);
+      if (__builtin_amdgcn_ballot_w64(m != 0u))
+        box_boundary_rule_table<T>(f, m, a.p.p_mask, a.p.rule_flags, faces);
+      bgk_collide<T>(f, a.p.omega, a.p.tau_f);
+      const unsigned r0 = F::kStochastic ? fmix32((nxy + unsigned(z1) * nplane) * 0x9e3779b1u + a.key0) : 0u;
+      S e[19];
+#pragma unroll
+      for (int k = 0; k < 19; ++k) e[k] = encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
+      complete(e);
+      if (live1) {
+#pragma unroll
+        for (int k = 0; k < 19; ++k) {
+          if (own_column(k)) continue;
+          const int slot = cz(k) < 0 ? 0 : (cz(k) == 0 ? s2 : s3);
+          (own + slot * ring_slot_planes(cz(k)) * PLANE)[(ring_first(cz(k)) + ring_rank(k)) * PLANE] = e[k];
+        }
+      }
+      e18_now = e[18];
+      e4_now = e[4];
+      e5 = e[5];
+    }
     __syncthreads();
-    // Step 2 on the interior of plane zz - 1, from LDS.
-    if (p >= 2 && wave < hyc && lane < w) {
-      const int z2 = zz - 1, y2 = y0 + wave, x2 = x0 + lane;
-      const int c = (wave + 1) * HX + lane + 1;  // the node's own cell
-      const int q0 = (p + 1) & 1, q1 = (p + 1) % 3;  // ring slots of rounds p - 1 (cz = 0) and p - 2 (cz = +1)
+    // Step 2 on the interior of plane zz - 1.
+    if (rows2 && zz > zb) {
+      const int z2 = zz - 1;
       T f[19];
 #pragma unroll
       for (int k = 0; k < 19; ++k) {
-        const int slot = ring_depth(k) == 1 ? 0 : (ring_depth(k) == 2 ? q0 : q1);
-        f[k] = Codec<S>::decode(ring[(ring_base(k) + slot) * PLANE + c - cy(k) * HX - cx(k)]);
+        if (own_column(k)) {
+          f[k] = Codec<S>::decode(k == 18 ? e18 : (k == 4 ? e4_before : e5));
+          continue;
+        }
+        const int slot = cz(k) < 0 ? 0 : (cz(k) == 0 ? 1 - s2 : s3_2);
+        f[k] = Codec<S>::decode((low + slot * ring_slot_planes(cz(k)) * PLANE)[
+            (ring_first(cz(k)) + ring_rank(k)) * PLANE + (1 - cy(k)) * HX + (1 - cx(k))]);
       }
-      rule_and_collide<T>(f, box_faces(a.p.bc_mask, x2, y2, z2, nx, ny, nz), a.p);
-      const unsigned n = (unsigned(z2) * unsigned(ny) + unsigned(y2)) * unsigned(nx) + unsigned(x2);
-      const unsigned r0 = F::kStochastic ? fmix32(n * 0x9e3779b1u + a.key1) : 0u;
-      const size_t row = size_t(unsigned(z2) * unsigned(ny) + unsigned(y2)) * rs;
-      if constexpr (kRowDescriptors) {
-        // the row is uniform over the wave: stores through its descriptor
-        const auto out = raw_buffer((S *)dst + row, unsigned(rs) * unsigned(sizeof(S)));
-        const unsigned pb = unsigned(ps) * unsigned(sizeof(S)), xo = unsigned(x2) * unsigned(sizeof(S));
+      const unsigned m = mxy | (z2 == 0 ? a.p.bc_mask & 16u : 0u) | (z2 == nz - 1 ? a.p.bc_mask & 32u : 0u);
+      if (__builtin_amdgcn_ballot_w64(m != 0u))
+        box_boundary_rule_table<T>(f, m, a.p.p_mask, a.p.rule_flags, faces);
+      bgk_collide<T>(f, a.p.omega, a.p.tau_f);
+      const unsigned r0 = F::kStochastic ? fmix32((nxy + unsigned(z2) * nplane) * 0x9e3779b1u + a.key1) : 0u;
+      S e[19];
 #pragma unroll
-        for (int k = 0; k < 19; ++k)
-          buf_store_nt<S>(encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u), out, xo, unsigned(k) * pb);
-      } else {
+      for (int k = 0; k < 19; ++k) e[k] = encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
+      complete(e);
+      complete(raw);
+      if (live1) {
+        const S *row = (const S *)((const char *)(S *)dst + (size_t(z2) * zbytes + size_t(__builtin_amdgcn_readfirstlane(y)) * rb));
+        const auto out = raw_buffer(row, unsigned(rb));
 #pragma unroll
-        for (int k = 0; k < 19; ++k)
-          store_elem<S, true>(dst + size_t(k) * ps + row + unsigned(x2),
-                              encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u));
+        for (int k = 0; k < 19; ++k) buf_store_nt<S>(e[k], out, xo[1], unsigned(k) * unsigned(pb));
       }
+    } else {
+      complete(raw);
     }
+    e18 = e18_now;
+    e4_before = e4;
+    e4 = e4_now;
+    s2 = 1 - s2;
+    s3 = s3 == 2 ? 0 : s3 + 1;
     __syncthreads();
   }
 }
 
-// Interior rows per tile of each storage form.  LDS holds 38 population
-// planes of 66 x (BYI + 2) elements: 147 KB for FP32 with BYI = 13 (one
-// workgroup of 16 waves per compute unit; step 1 then costs 1.2 times the
-// updates it feeds), 137 KB for FP64 with BYI = 5, 73 KB for FP16 with
-// BYI = 13.
+// Interior rows per tile of each storage form.  LDS holds 32 population
+// planes of 66 x (BYI + 2) elements: 127 KB for FP32 with BYI = 13 (one
+// workgroup of 16 waves per compute unit, the most a workgroup can have;
+// step 1 then costs 1.2 times the updates it feeds), 152 KB for FP64 with
+// BYI = 7 (the most that fits), 63 KB for FP16 with BYI = 13.
 template <class F>
 struct Sweep2Rows;
 template <>
 struct Sweep2Rows<FormF64> {
-  static constexpr int kBYI = 5;
+  static constexpr int kBYI = 7;
 };
 template <>
 struct Sweep2Rows<FormF32> {
