@@ -475,7 +475,7 @@ lbm_status lbm_step(lbm_lattice *L, int nsteps) {
   lbm::SweepConfig c = sweep_config(L);
   const bool ext = L->d_solid || L->d_geo || L->d_face_v[0] || L->d_face_v[1] || L->d_face_v[2] ||
                    L->d_face_v[3] || L->d_face_v[4] || L->d_face_v[5];
-  const bool two = L->pass_steps == 2 && lbm::sweep2_takes(L->lay, L->storage) && !ext;
+  const bool two = L->pass_steps == 2 && lbm::sweep2_takes(L->lay, L->ny, L->storage) && !ext;
   for (int s = 0; s < nsteps;) {
     c.step = unsigned(L->steps);
     const bool pair = two && nsteps - s >= 2;
@@ -696,7 +696,7 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
       if (xcd == LBM_XCD_ROWS && sh[0] * sh[1] >= L->nx) continue;
       cands.push_back({1, sh[0], sh[1], xcd, 0, 0});
     }
-  if (lbm::sweep2_takes(L->lay, L->storage) && !ext)
+  if (lbm::sweep2_takes(L->lay, L->ny, L->storage) && !ext)
     for (int zc : {16, 32, 64})
       for (int rows : {0, 5, 12}) {
         if (rows != 0 && L->storage == LBM_STORE_F64) continue;  // FP64 tiles have 7 rows either way

@@ -105,10 +105,10 @@ size_t sweep_delta_partials(const SweepConfig &c);
 // Two steps (c.step and c.step + 1) in one pass, row-major layout, no solid
 // mask, face field or geometry; z ranges of zc planes per workgroup; tiles of
 // `rows` interior rows (5, or 0 for the form's default).
-// Whether the pass takes a layout: row-major (the tile's rows are whole rows
-// of one population), a row's bytes within a buffer descriptor's 32-bit
-// offsets.
-bool sweep2_takes(const PopLayout &lay, int storage);
+// Whether the pass takes a lattice: row-major (the tile's rows are whole rows
+// of one population), a z plane's bytes within the 32-bit offsets of a buffer
+// descriptor.
+bool sweep2_takes(const PopLayout &lay, int ny, int storage);
 hipError_t launch_sweep2(const SweepConfig &c, int zc, int rows, const void *src, void *dst, hipStream_t s);
 
 // Node codes of a complex geometry from node types (0 fluid, 1 wall node,

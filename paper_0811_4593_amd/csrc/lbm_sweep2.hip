@@ -71,13 +71,13 @@ static hipError_t launch_sweep2_t(const SweepConfig &c, int zc, const void *src,
   return hipGetLastError();
 }
 
-bool sweep2_takes(const PopLayout &lay, int storage) {
+bool sweep2_takes(const PopLayout &lay, int ny, int storage) {
   const size_t esize = storage == kStoreF64 ? 8 : (storage == kStoreF32 ? 4 : 2);
-  return lay.row_stride == 19 * lay.pop_stride && lay.row_stride * esize < (size_t(1) << 32);
+  return lay.row_stride == 19 * lay.pop_stride && lay.row_stride * esize * size_t(ny) < (size_t(1) << 32);
 }
 
 hipError_t launch_sweep2(const SweepConfig &c, int zc, int rows, const void *src, void *dst, hipStream_t s) {
-  if (!sweep2_takes(c.layout, c.storage) || zc < 1) return hipErrorInvalidValue;
+  if (!sweep2_takes(c.layout, c.ny, c.storage) || zc < 1) return hipErrorInvalidValue;
   switch (c.storage) {
     case kStoreF64: return launch_sweep2_t<FormF64, Sweep2Rows<FormF64>::kBYI>(c, zc, src, dst, s);
     case kStoreF32:

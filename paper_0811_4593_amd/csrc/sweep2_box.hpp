@@ -76,9 +76,12 @@ struct Sweep2Tile {
   static constexpr int kWaves = BYI <= 5 ? 4 : (BYI + 3 + 3) / 4;
 };
 
-// Fix the point in the program where a node's 19 values are complete: values
-// from memory have been waited for, computed ones are in registers, and
-// nothing on them moves across.
+// Every load issued so far has returned (vmcnt 0; gfx9 encoding with the
+// other counters at their maxima).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
+// Fix the point in the program where a node's 19 values are complete:
+// nothing that computes them moves below.
 template <class V>
 __device__ __forceinline__ void complete(V (&v)[19]) {
   asm volatile(""
@@ -115,7 +118,6 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
   using T = typename Codec<S>::T;
   using Tile = Sweep2Tile<F, BYI>;
   constexpr int HX = Tile::kHX, HY = Tile::kHY, PLANE = Tile::kPlane;
-  typedef global_ptr<const char> BytesIn;
   __shared__ T faces[6][4];  // velocity and density of each face
   if (threadIdx.x < 6u) {
     const unsigned b = threadIdx.x;
@@ -148,35 +150,31 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
   const unsigned mxy = box_faces(a.p.bc_mask & 15u, x, y, -1, nx, ny, nz);
   const unsigned nxy = unsigned(y) * unsigned(nx) + unsigned(x);
   const unsigned nplane = unsigned(nx) * unsigned(ny);
-  const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
-  const int ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
-  // lane byte offsets within a row, index c + 1 -> coordinate - c
-  const unsigned xo[3] = {unsigned(xp) * unsigned(sizeof(S)), unsigned(x) * unsigned(sizeof(S)),
-                          unsigned(xm) * unsigned(sizeof(S))};
-  const size_t pb = a.pop_stride * sizeof(S), rb = a.row_stride * sizeof(S), zbytes = rb * size_t(ny);
-
-  // Sources of the lane's node at plane z.  A row wave's rows are uniform:
-  // scalar bases plus the lane's x offset; the halo-column wave's differ by
-  // lane.
+  // Sources and destination of the lane's node.  A z plane's bytes fit 32
+  // bits: one descriptor per plane (base at the plane's start, advanced from
+  // round to round), the lane's offset within the plane for each of the nine
+  // (cx, cy), and the population's start as scalar offset -- nothing per load
+  // is recomputed in the loop, and the halo-column wave, whose rows differ by
+  // lane, runs the same code.
+  const unsigned rb = unsigned(a.row_stride) * unsigned(sizeof(S)), pb = unsigned(a.pop_stride) * unsigned(sizeof(S));
+  const size_t zbytes = size_t(rb) * size_t(ny);
+  unsigned off[3][3];  // [cy + 1][cx + 1]
+  {
+    const unsigned xs[3] = {x == nx - 1 ? 0u : unsigned(x) + 1u, unsigned(x), x == 0 ? unsigned(nx) - 1u : unsigned(x) - 1u};
+    const unsigned ys[3] = {y == ny - 1 ? 0u : unsigned(y) + 1u, unsigned(y), y == 0 ? unsigned(ny) - 1u : unsigned(y) - 1u};
+#pragma unroll
+    for (int cyi = 0; cyi < 3; ++cyi)
+#pragma unroll
+      for (int cxi = 0; cxi < 3; ++cxi) off[cyi][cxi] = ys[cyi] * rb + xs[cxi] * unsigned(sizeof(S));
+  }
+  const char *const in = (const char *)(const S *)src, *const out = (const char *)(S *)dst;
+  const char *plane[3];  // sources of the plane being loaded, index cz + 1: planes z + 1, z, z - 1
   S raw[19];
-  auto load = [&](int z) {
-    const int zs[3] = {z == nz - 1 ? 0 : z + 1, z, z == 0 ? nz - 1 : z - 1};
-    if (!columns) {
-      const int yu[3] = {__builtin_amdgcn_readfirstlane(yp), __builtin_amdgcn_readfirstlane(y),
-                         __builtin_amdgcn_readfirstlane(ym)};
+  // bytes: the plane's, or 0 to read nothing
+  auto load = [&](unsigned bytes) {
 #pragma unroll
-      for (int k = 0; k < 19; ++k) {
-        const S *row = (const S *)((const char *)(const S *)src + (size_t(zs[cz(k) + 1]) * zbytes + size_t(yu[cy(k) + 1]) * rb));
-        raw[k] = buf_load<S>(raw_buffer(row, unsigned(rb)), xo[cx(k) + 1], unsigned(k) * unsigned(pb));
-      }
-    } else {
-      const size_t yo[3] = {size_t(yp) * rb, size_t(y) * rb, size_t(ym) * rb};
-#pragma unroll
-      for (int k = 0; k < 19; ++k) {
-        const BytesIn plane = (BytesIn)src + (size_t(zs[cz(k) + 1]) * zbytes + size_t(k) * pb);
-        raw[k] = *(global_ptr<const S>)(plane + (yo[cy(k) + 1] + xo[cx(k) + 1]));
-      }
-    }
+    for (int k = 0; k < 19; ++k)
+      raw[k] = buf_load<S>(raw_buffer(plane[cz(k) + 1], bytes), off[cy(k) + 1][cx(k) + 1], unsigned(k) * pb);
   };
 
   // LDS cells: `out` the lane's own cell, `in` the lowest cell step 2 reads.
@@ -184,8 +182,14 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
   const S *const low = own - HX - 1;
   S e18 = S(0), e4 = S(0), e4_before = S(0), e5 = S(0);  // own column: rest, +z (one and two rounds back), -z
   __syncthreads();  // the face table
-  load(zb == 0 ? nz - 1 : zb - 1);
-  complete(raw);
+  int zp = zb;  // the plane of plane[0], one above the one being loaded
+  const int zm = zb == 0 ? nz - 1 : zb - 1;
+  plane[2] = in + size_t(zm == 0 ? nz - 1 : zm - 1) * zbytes;
+  plane[1] = in + size_t(zm) * zbytes;
+  plane[0] = in + size_t(zp) * zbytes;
+  const char *out_plane = out + size_t(zb) * zbytes;
+  load(unsigned(zbytes));
+  wait_loads();
   int s2 = 0, s3 = 0;  // ring slots of this round: p mod 2, p mod 3
   for (int zz = zb - 1; zz <= ze; ++zz) {
     const int z1 = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
@@ -194,7 +198,11 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
 #pragma unroll
     for (int k = 0; k < 19; ++k) f[k] = Codec<S>::decode(raw[k]);
     complete(f);
-    load(zz == ze ? z1 : (z1 == nz - 1 ? 0 : z1 + 1));
+    zp = zp == nz - 1 ? 0 : zp + 1;
+    plane[2] = plane[1];
+    plane[1] = plane[0];
+    plane[0] = zp == 0 ? in : plane[0] + zbytes;
+    load(zz < ze ? unsigned(zbytes) : 0u);
     S e18_now = S(0), e4_now = S(0);
     if (rows1) {
       const unsigned m = mxy | (z1 == 0 ? a.p.bc_mask & 16u : 0u) | (z1 == nz - 1 ? a.p.bc_mask & 32u : 0u);
@@ -242,15 +250,15 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
 #pragma unroll
       for (int k = 0; k < 19; ++k) e[k] = encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
       complete(e);
-      complete(raw);
+      wait_loads();
       if (live1) {
-        const S *row = (const S *)((const char *)(S *)dst + (size_t(z2) * zbytes + size_t(__builtin_amdgcn_readfirstlane(y)) * rb));
-        const auto out = raw_buffer(row, unsigned(rb));
+        const auto to = raw_buffer(out_plane, unsigned(zbytes));
 #pragma unroll
-        for (int k = 0; k < 19; ++k) buf_store_nt<S>(e[k], out, xo[1], unsigned(k) * unsigned(pb));
+        for (int k = 0; k < 19; ++k) buf_store_nt<S>(e[k], to, off[1][1], unsigned(k) * pb);
       }
+      out_plane += zbytes;
     } else {
-      complete(raw);
+      wait_loads();
     }
     e18 = e18_now;
     e4_before = e4;
