@@ -10,6 +10,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace lbm {
 
 __host__ __device__ constexpr int cx(int k) {
@@ -63,6 +65,23 @@ struct FaceVel {
   T v[6][3];
 };
 
+// a * b + c, rounded once.  The rules and the collision write their
+// multiply-adds out and switch the compiler's own contraction off: which
+// products it fuses depends on the code around a call, and every kernel that
+// advances a lattice has to give the same bits.
+__device__ __forceinline__ double fused_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fused_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// a / den with inv = 1 / den rounded to nearest: the quotient a * inv
+// corrected once by its exact remainder is the rounded quotient (Markstein,
+// IBM J. Res. Dev. 34(1), 1990), in three operations where the division takes
+// about twelve, one after the other.
+template <class T>
+__device__ __forceinline__ T quotient(T a, T den, T inv) {
+  const T q = a * inv;
+  return fused_add(fused_add(-den, q, a), inv, q);
+}
+
 // Per-lattice parameters of the node update.
 template <class T>
 struct NodeParams {
@@ -73,6 +92,8 @@ struct NodeParams {
   FaceVel<T> fv;     // velocity faces: the velocity; pressure faces: the
                      // tangential velocity (normal component zero)
   T rho_p[6];        // prescribed density of each pressure face
+  T den[6], inv[6];  // divisor of the face's bracket, 1 - v.n (velocity face)
+                     // or rho_p (pressure face), and its reciprocal
   unsigned rule_flags;  // kRuleNoTransverse: face rule without the corrections N
 };
 
@@ -148,163 +169,220 @@ __device__ __forceinline__ void face_values(unsigned m, const NodeParams<T> &p, 
 //   corner form): in deviations (rho0 - 1 - s) / 14 (edge) or / 18 (corner),
 //   s the sum of the other moving populations.
 // ---------------------------------------------------------------------------
+// Every rule is computed by all lanes of a wave in which some lane needs it
+// and selected where it applies (mine): no divergent branches around it, and
+// no register copies where they would join.  The few waves with boundary
+// nodes are the ones the others of a workgroup wait for, so what counts is
+// the length of the rules' dependent chains: in the two-step pass a plane of
+// a workgroup at the faces took 7.4 us, 4.5 us with no rules at all.  This
+// form against divergent branches and divisions: 256 x 128 x 128 FP32 0.110
+// -> 0.100 ms per step, 64 x 64 x 65 FP64 17.1 -> 15.6 us, 512 x 256 x 256
+// FP16 0.494 -> 0.458 ms.
+
+// Values of one face.
+template <class T>
+struct FaceVals {
+  T v[3], r0;   // velocity or tangential velocity, prescribed density
+  T den, inv;   // as NodeParams
+};
+
+// Divisor of the bracket of face b with velocity v or density r0.
+template <class T, int b>
+__host__ __device__ __forceinline__ T face_divisor(bool pressure, const T (&v)[3], T r0) {
+  return pressure ? r0 : T(1) - T(face_normal(b, b / 2)) * v[b / 2];
+}
+
 // Face rule of face b (one bit of m; b a compile-time constant, so the set of
 // unknowns U, the normal n and every population index are constants and only
-// the unknowns' updates are computed).  (vx, vy, vz, r0): the face values
-// (the face's parameters, or a per-node field); pressure: b is a pressure
-// face.  The sums run in population order and skip only terms that are
-// exactly +0 in the masked form of the rule, so the result does not depend
-// on whether the face is known at compile time.
+// the unknowns' updates are computed).  pressure: b is a pressure face.  The
+// sums run in population order.
 template <class T, int b>
-__device__ __forceinline__ void face_rule(T (&d)[19], bool pressure, T keep_n, T vx, T vy, T vz, T r0) {
+__device__ __forceinline__ void face_rule(T (&d)[19], bool mine, bool pressure, T keep_n, const FaceVals<T> &f) {
+#pragma clang fp contract(off)
   constexpr unsigned U = unknown_mask(b);
-  constexpr int sx = face_normal(b, 0), sy = face_normal(b, 1), sz = face_normal(b, 2);
-  T s_known = T(0), s_out = T(0), Mx = T(0), My = T(0), Mz = T(0);
+  constexpr int s = face_normal(b, b / 2), ax = b / 2;
+  T s_known = T(0), s_out = T(0), M[3] = {T(0), T(0), T(0)};
 #pragma unroll
   for (int k = 0; k < 19; ++k) {
     const bool unk = (U >> k) & 1u;
     const bool out = (U >> opp(k)) & 1u;  // c_k.n < 0
-    const bool in_plane = !unk && !out;
+    const int c[3] = {cx(k), cy(k), cz(k)};
     if (!unk) s_known += d[k];
     if (out) s_out += d[k];
-    if (cx(k) && in_plane) Mx += T(cx(k)) * d[k];
-    if (cy(k) && in_plane) My += T(cy(k)) * d[k];
-    if (cz(k) && in_plane) Mz += T(cz(k)) * d[k];
+    if (!unk && !out)
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        if (c[a]) M[a] += T(c[a]) * d[k];
   }
   const T B = T(1) + s_known + s_out;
-  T rho = r0;
+  const T q = quotient(B, f.den, f.inv);
+  T v[3] = {f.v[0], f.v[1], f.v[2]}, rho = q;
   if (pressure) {
-    const T vn_p = T(1) - B / r0;  // normal velocity from rho0
-    vx = vx + T(sx) * vn_p;
-    vy = vy + T(sy) * vn_p;
-    vz = vz + T(sz) * vn_p;
+    v[ax] += T(s) * (T(1) - q);  // normal velocity from the density
+    rho = f.r0;
   }
-  const T vn = T(sx) * vx + T(sy) * vy + T(sz) * vz;
-  if (!pressure) rho = B / (T(1) - vn);
-  const T rho3 = rho / T(3);
+  const T vn = T(s) * v[ax];
+  const T rho3 = quotient(rho, T(3), T(1) / T(3));
 #pragma unroll
   for (int j = 0; j < 18; ++j) {
     if (!((U >> j) & 1u)) continue;
     const int i = opp(j);
-    const T civ = T(cx(i)) * vx + T(cy(i)) * vy + T(cz(i)) * vz;
-    const T ciM = T(cx(i)) * Mx + T(cy(i)) * My + T(cz(i)) * Mz;
-    d[j] = d[i] - T(6 * w36(i)) / T(36) * rho * civ + keep_n * (T(0.5) * ciM - rho3 * (civ + vn));
+    const int c[3] = {cx(i), cy(i), cz(i)};
+    T civ = T(c[ax]) * v[ax], ciM = T(0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      if (c[a] && a != ax) {
+        civ += T(c[a]) * v[a];
+        ciM = T(c[a]) * M[a];
+      }
+    const T e = fused_add(-(T(6 * w36(i)) / T(36) * rho), civ, d[i]);
+    const T n = fused_add(T(0.5), ciM, -(rho3 * (civ + vn)));
+    const T dj = fused_add(keep_n, n, e);
+    d[j] = mine ? dj : d[j];
   }
 }
 
 // Edge (two bits of m) or corner (three bits), no-slip; r0: the density of a
 // bordering pressure face when there is one (pressure; at most one, as
-// pressure faces lie on one axis).
+// pressure faces lie on one axis).  mine: m has two or three bits.
 template <class T>
-__device__ __forceinline__ void edge_corner_rule(T (&d)[19], unsigned m, bool pressure, T r0) {
-  unsigned U = 0;
+__device__ __forceinline__ void edge_corner_rule(T (&d)[19], bool mine, unsigned m, bool pressure, T r0) {
+#pragma clang fp contract(off)
+  // Populations that enter (U) and leave (O) through the node's plane on each
+  // axis; buried: entering through one plane and leaving through another.
+  unsigned U[3], O[3];
 #pragma unroll
-  for (int b = 0; b < 6; ++b)
-    if (m & (1u << b)) U |= unknown_mask(b);
-  // Sum of inward normals, one component per axis.
-  const int sx = int(m & 1u) - int((m >> 1) & 1u);
-  const int sy = int((m >> 2) & 1u) - int((m >> 3) & 1u);
-  const int sz = int((m >> 4) & 1u) - int((m >> 5) & 1u);
-  const int nb = __popc(m);
-  const int ex = (nb == 2 && sx == 0) ? 1 : 0;
-  const int ey = (nb == 2 && sy == 0) ? 1 : 0;
-  const int ez = (nb == 2 && sz == 0) ? 1 : 0;
-  const T Pq = T(0.25) * (T(ex) * (d[0] - d[1]) + T(ey) * (d[2] - d[3]) + T(ez) * (d[4] - d[5]));
-  unsigned bur = 0;
+  for (int a = 0; a < 3; ++a) {
+    const bool lo = (m >> (2 * a)) & 1u, hi = (m >> (2 * a + 1)) & 1u;
+    U[a] = lo ? unknown_mask(2 * a) : (hi ? unknown_mask(2 * a + 1) : 0u);
+    O[a] = lo ? unknown_mask(2 * a + 1) : (hi ? unknown_mask(2 * a) : 0u);
+  }
+  unsigned bur = (U[0] & (O[1] | O[2])) | (U[1] & (O[0] | O[2])) | (U[2] & (O[0] | O[1]));
+  unsigned bounced = (U[0] | U[1] | U[2]) & ~bur;
+  bur = mine ? bur : 0u;
+  bounced = mine ? bounced : 0u;
+  const bool edge = __popc(m) == 2;
+  // A quarter of the momentum along the edge, on the axis of an edge node
+  // that has no plane.
+  T P[3];
 #pragma unroll
-  for (int k = 0; k < 18; ++k) bur |= ((U >> k) & (U >> opp(k)) & 1u) << k;
+  for (int a = 0; a < 3; ++a) P[a] = edge && U[a] == 0u ? T(0.25) * (d[2 * a] - d[2 * a + 1]) : T(0);
+  // Of two opposite links at most one is bounced back.
 #pragma unroll
   for (int k = 0; k < 18; ++k) {
-    const bool bounced = ((U & ~bur) >> k) & 1u;
-    const int ce = cx(k) * ex + cy(k) * ey + cz(k) * ez;
-    const T dk = d[opp(k)] - T(ce) * Pq;
-    d[k] = bounced ? dk : d[k];
+    const int o = opp(k);
+    if (o < k) continue;
+    T to_k = d[o], to_o = d[k];
+    const int c[3] = {cx(k), cy(k), cz(k)};
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      if (c[a]) {
+        to_k -= T(c[a]) * P[a];
+        to_o += T(c[a]) * P[a];
+      }
+    const T dk = d[k];
+    d[k] = ((bounced >> k) & 1u) ? to_k : dk;
+    d[o] = ((bounced >> o) & 1u) ? to_o : d[o];
   }
   T s = T(0);
 #pragma unroll
   for (int k = 0; k < 18; ++k) s += ((bur >> k) & 1u) ? T(0) : d[k];
-  const T db_v = s / (nb == 2 ? T(22) : T(18));
-  const T db_p = (r0 - T(1) - s) / (nb == 2 ? T(14) : T(18));
-  const T db = pressure ? db_p : db_v;
+  T db = quotient(s, edge ? T(22) : T(18), edge ? T(1) / T(22) : T(1) / T(18));
+  if (__builtin_amdgcn_ballot_w64(pressure)) {
+    const T db_p = quotient(r0 - T(1) - s, edge ? T(14) : T(18), edge ? T(1) / T(14) : T(1) / T(18));
+    db = pressure ? db_p : db;
+  }
 #pragma unroll
-  for (int k = 0; k < 18; ++k) d[k] = ((bur >> k) & 1u) ? db : d[k];
-  d[18] = T(12) * db;
+  for (int k = 6; k < 18; ++k) d[k] = ((bur >> k) & 1u) ? db : d[k];  // axis links are never buried
+  d[18] = mine ? T(12) * db : d[18];
+}
+
+// Boundary rule of a node with face mask m: the face rules a wave's lanes
+// need, then the edge and corner rule.  vals(b): the FaceVals of face b (b a
+// std::integral_constant); pmask: the pressure faces among m's faces (p_mask
+// for box faces, 0 for the walls of a complex geometry); density(pm): that
+// of the pressure face in pm.
+template <class T, class Vals, class Density>
+__device__ __forceinline__ void apply_boundary_rule(T (&d)[19], unsigned m, unsigned pmask, unsigned rule_flags,
+                                                    const Vals &vals, const Density &density) {
+  const T keep_n = (rule_flags & kRuleNoTransverse) ? T(0) : T(1);
+#define LBM_FACE(b)                                         \
+  if (__builtin_amdgcn_ballot_w64(m == (1u << (b))))        \
+    face_rule<T, b>(d, m == (1u << (b)), ((pmask >> (b)) & 1u) != 0u, keep_n, vals(std::integral_constant<int, b>()));
+  LBM_FACE(0)
+  LBM_FACE(1)
+  LBM_FACE(2)
+  LBM_FACE(3)
+  LBM_FACE(4)
+  LBM_FACE(5)
+#undef LBM_FACE
+  const bool corner = (m & (m - 1u)) != 0u;
+  if (__builtin_amdgcn_ballot_w64(corner)) {
+    const unsigned pm = m & pmask;
+    edge_corner_rule<T>(d, corner, m, pm != 0u, density(pm));
+  }
 }
 
 // Density of the pressure face among the faces pm (at most one bit).
-template <class T>
-__device__ __forceinline__ T edge_density(unsigned pm, const T (&rho_p)[6]) {
+template <class T, class Rho>
+__device__ __forceinline__ T edge_density(unsigned pm, const Rho &rho) {
   T r0 = T(1);
 #pragma unroll
   for (int b = 0; b < 6; ++b)
-    if (pm & (1u << b)) r0 = rho_p[b];
+    if (pm & (1u << b)) r0 = rho(b);
   return r0;
 }
 
-// Boundary rule of a node with face mask m and given face values (a
-// per-node velocity field, or the walls of a complex geometry): each lane
-// runs the rule of its own face, edge or corner; a wave runs only the face
-// rules its lanes need.  (vx, vy, vz, r0): the face values of a face node;
-// not used on edges and corners.  pmask: the pressure faces among m's faces
-// (p.p_mask for box faces, 0 for the walls of a complex geometry).
+// With face values per lane (a per-node velocity field, or the walls of a
+// complex geometry).  (vx, vy, vz, r0): not used on edges and corners.
 template <class T>
 __device__ __forceinline__ void boundary_rule(T (&d)[19], unsigned m, const NodeParams<T> &p, unsigned pmask, T vx,
                                               T vy, T vz, T r0) {
-  const T keep_n = (p.rule_flags & kRuleNoTransverse) ? T(0) : T(1);
-  if (m == 1u) face_rule<T, 0>(d, (pmask & 1u) != 0u, keep_n, vx, vy, vz, r0);
-  if (m == 2u) face_rule<T, 1>(d, (pmask & 2u) != 0u, keep_n, vx, vy, vz, r0);
-  if (m == 4u) face_rule<T, 2>(d, (pmask & 4u) != 0u, keep_n, vx, vy, vz, r0);
-  if (m == 8u) face_rule<T, 3>(d, (pmask & 8u) != 0u, keep_n, vx, vy, vz, r0);
-  if (m == 16u) face_rule<T, 4>(d, (pmask & 16u) != 0u, keep_n, vx, vy, vz, r0);
-  if (m == 32u) face_rule<T, 5>(d, (pmask & 32u) != 0u, keep_n, vx, vy, vz, r0);
-  if (m & (m - 1u)) edge_corner_rule<T>(d, m, (m & pmask) != 0u, edge_density<T>(m & pmask, p.rho_p));
+  apply_boundary_rule<T>(
+      d, m, pmask, p.rule_flags,
+      [&](auto b) {
+        FaceVals<T> f{{vx, vy, vz}, r0, T(1), T(1)};
+        f.den = face_divisor<T, b()>(((pmask >> b()) & 1u) != 0u, f.v, r0);
+        f.inv = T(1) / f.den;
+        return f;
+      },
+      [&](unsigned pm) { return edge_density<T>(pm, [&](int b) { return p.rho_p[b]; }); });
 }
 
-// Boundary rule of a node of a box whose faces take the lattice's face
-// parameters (velocity, or tangential velocity and density of a pressure
-// face): as boundary_rule, with the face values read directly.
+// Of a box whose faces take the lattice's face parameters.
 template <class T>
 __device__ __forceinline__ void box_boundary_rule(T (&d)[19], unsigned m, const NodeParams<T> &p) {
-  const T keep_n = (p.rule_flags & kRuleNoTransverse) ? T(0) : T(1);
-#define LBM_FACE(b)                                                                                        \
-  if (m == (1u << (b)))                                                                                    \
-    face_rule<T, b>(d, ((p.p_mask >> (b)) & 1u) != 0u, keep_n, p.fv.v[b][0], p.fv.v[b][1], p.fv.v[b][2], \
-                    p.rho_p[b]);
-  LBM_FACE(0)
-  LBM_FACE(1)
-  LBM_FACE(2)
-  LBM_FACE(3)
-  LBM_FACE(4)
-  LBM_FACE(5)
-#undef LBM_FACE
-  if (m & (m - 1u)) edge_corner_rule<T>(d, m, (m & p.p_mask) != 0u, edge_density<T>(m & p.p_mask, p.rho_p));
+  apply_boundary_rule<T>(
+      d, m, p.p_mask, p.rule_flags,
+      [&](auto b) {
+        return FaceVals<T>{{p.fv.v[b()][0], p.fv.v[b()][1], p.fv.v[b()][2]}, p.rho_p[b()], p.den[b()], p.inv[b()]};
+      },
+      [&](unsigned pm) { return edge_density<T>(pm, [&](int b) { return p.rho_p[b]; }); });
 }
 
-// As box_boundary_rule, with the face values in a table in LDS, tab[b] =
-// (velocity, density) of face b: a kernel that runs the rule inside a loop
-// keeps no scalar registers for the 24 values (the compiler otherwise holds
-// them across the loop and spills).
+// The same with the face values in a table in LDS: a kernel that runs the
+// rule inside a loop keeps no scalar registers for them (the compiler
+// otherwise holds them across the loop and spills).
 template <class T>
 __device__ __forceinline__ void box_boundary_rule_table(T (&d)[19], unsigned m, unsigned p_mask, unsigned rule_flags,
-                                                        const T (*tab)[4]) {
-  const T keep_n = (rule_flags & kRuleNoTransverse) ? T(0) : T(1);
-#define LBM_FACE(b)              \
-  if (m == (1u << (b)))          \
-    face_rule<T, b>(d, ((p_mask >> (b)) & 1u) != 0u, keep_n, tab[b][0], tab[b][1], tab[b][2], tab[b][3]);
-  LBM_FACE(0)
-  LBM_FACE(1)
-  LBM_FACE(2)
-  LBM_FACE(3)
-  LBM_FACE(4)
-  LBM_FACE(5)
-#undef LBM_FACE
-  if (m & (m - 1u)) {
-    const unsigned pm = m & p_mask;
-    T r0 = T(1);
-#pragma unroll
-    for (int b = 0; b < 6; ++b)
-      if (pm & (1u << b)) r0 = tab[b][3];
-    edge_corner_rule<T>(d, m, pm != 0u, r0);
+                                                        const FaceVals<T> *tab) {
+  apply_boundary_rule<T>(
+      d, m, p_mask, rule_flags, [&](auto b) { return tab[b()]; },
+      [&](unsigned pm) { return edge_density<T>(pm, [&](int b) { return tab[b].r0; }); });
+}
+
+// Fill the divisors of every face from its velocity or density.
+template <class T>
+__host__ __device__ inline void set_face_divisors(NodeParams<T> &p) {
+  const T d[6] = {face_divisor<T, 0>(p.p_mask & 1u, p.fv.v[0], p.rho_p[0]),
+                  face_divisor<T, 1>(p.p_mask & 2u, p.fv.v[1], p.rho_p[1]),
+                  face_divisor<T, 2>(p.p_mask & 4u, p.fv.v[2], p.rho_p[2]),
+                  face_divisor<T, 3>(p.p_mask & 8u, p.fv.v[3], p.rho_p[3]),
+                  face_divisor<T, 4>(p.p_mask & 16u, p.fv.v[4], p.rho_p[4]),
+                  face_divisor<T, 5>(p.p_mask & 32u, p.fv.v[5], p.rho_p[5])};
+  for (int f = 0; f < 6; ++f) {
+    p.den[f] = d[f];
+    p.inv[f] = T(1) / d[f];
   }
 }
 
@@ -382,12 +460,6 @@ __device__ __forceinline__ void general_wall_rule(T (&d)[19], unsigned U) {
 //   d_k <- d_k + omega (d_k^eq - d_k), omega = 1/tau, c_s^2 = 1/3.
 // A body force F enters as the velocity shift tau F / rho inside f^eq
 // (eq_gravity): u = (sum d c + tau F) / rho.
-//
-// Every multiply-add is written out (fused_add) and the compiler's own
-// contraction is off: which products it fuses depends on the code around the
-// call, and every kernel that advances a lattice has to give the same bits.
-__device__ __forceinline__ double fused_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fused_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // c_k . u of a diagonal link is one component's momentum times 1 / rho fused
 // with the other component's velocity; whether the first component is the

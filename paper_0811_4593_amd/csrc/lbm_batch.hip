@@ -44,6 +44,7 @@ struct BatchLat {
   double omega;    // 1 / tau
   double v[6][3];  // face velocities (pressure faces: tangential velocity)
   double rho_p[6]; // prescribed densities of the pressure faces
+  double den[6], inv[6];  // NodeParams::den and inv, evaluated in the storage form's arithmetic
   double tau_f[3]; // tau * body force
   double inv_uref; // 1 / velocity scale of the convergence measure
 };
@@ -93,7 +94,11 @@ __device__ __forceinline__ NodeParams<T> lattice_params(const BatchLat &L) {
   prm.rule_flags = 0u;
   prm.omega = T(L.omega);
 #pragma unroll
-  for (int f = 0; f < 6; ++f) prm.rho_p[f] = T(L.rho_p[f]);
+  for (int f = 0; f < 6; ++f) {
+    prm.rho_p[f] = T(L.rho_p[f]);
+    prm.den[f] = T(L.den[f]);
+    prm.inv[f] = T(L.inv[f]);
+  }
 #pragma unroll
   for (int d = 0; d < 3; ++d) prm.tau_f[d] = T(L.tau_f[d]);
 #pragma unroll
@@ -391,6 +396,23 @@ static hipError_t launch_batch_pass(int storage, const BatchLat *lats, const Bat
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// The divisors of a lattice's faces in the arithmetic type T (each value is
+// exact in double).
+template <class T>
+static void set_lattice_divisors(BatchLat &L) {
+  NodeParams<T> p;
+  p.p_mask = L.p_mask;
+  for (int f = 0; f < 6; ++f) {
+    p.rho_p[f] = T(L.rho_p[f]);
+    for (int d = 0; d < 3; ++d) p.fv.v[f][d] = T(L.v[f][d]);
+  }
+  set_face_divisors<T>(p);
+  for (int f = 0; f < 6; ++f) {
+    L.den[f] = double(p.den[f]);
+    L.inv[f] = double(p.inv[f]);
+  }
 }
 
 static hipError_t launch_batch_delta(int storage, const BatchLat *lats, const BatchTile *tiles, const int *nt,
@@ -1040,6 +1062,10 @@ lbm_status admit(lbm_batch *B) {
       for (int d = 0; d < 3; ++d) L.v[f][d] -= un * lbm::kFaceNormal[f][d];
       L.rho_p[f] = J.spec.bc_rho[f];
     }
+    if (esize == 2)
+      lbm::set_lattice_divisors<float>(L);
+    else
+      lbm::set_lattice_divisors<double>(L);
     for (int d = 0; d < 3; ++d) L.tau_f[d] = J.spec.tau * J.spec.force[d];
     L.inv_uref = 1.0 / J.spec.u_ref;
     // the same lattice as a single-lattice sweep (a chunk that steps this job alone)

@@ -338,6 +338,7 @@ static SweepArgs<T> make_args(const SweepConfig &c) {
   a.key = step_key(c.step);
   for (int f = 0; f < 6; ++f)
     for (int d = 0; d < 3; ++d) a.p.fv.v[f][d] = T(c.v[f][d]);
+  set_face_divisors<T>(a.p);
   return a;
 }
 

@@ -63,6 +63,7 @@ static hipError_t launch_sweep2_t(const SweepConfig &c, int zc, const void *src,
   for (int f = 0; f < 6; ++f) a.p.rho_p[f] = T(c.rho_p[f]);
   for (int f = 0; f < 6; ++f)
     for (int d = 0; d < 3; ++d) a.p.fv.v[f][d] = T(c.v[f][d]);
+  set_face_divisors<T>(a.p);
   const size_t tiles_z = (size_t(c.nz) + size_t(zc) - 1) / size_t(zc);
   const size_t nblocks = size_t(a.tiles_x) * size_t(a.tiles_y) * tiles_z;
   if (nblocks == 0 || nblocks > 0x7fffffffu) return hipErrorInvalidValue;

@@ -118,17 +118,11 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
   using T = typename Codec<S>::T;
   using Tile = Sweep2Tile<F, BYI>;
   constexpr int HX = Tile::kHX, HY = Tile::kHY, PLANE = Tile::kPlane;
-  __shared__ T faces[6][4];  // velocity and density of each face
-  if (threadIdx.x < 6u) {
-    const unsigned b = threadIdx.x;
+  __shared__ FaceVals<T> faces[6];
 #pragma unroll
-    for (unsigned f = 0; f < 6u; ++f)
-      if (b == f) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) faces[f][d] = a.p.fv.v[f][d];
-        faces[f][3] = a.p.rho_p[f];
-      }
-  }
+  for (unsigned f = 0; f < 6u; ++f)
+    if (threadIdx.x == f)
+      faces[f] = FaceVals<T>{{a.p.fv.v[f][0], a.p.fv.v[f][1], a.p.fv.v[f][2]}, a.p.rho_p[f], a.p.den[f], a.p.inv[f]};
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int x0 = int(tx) * 64, y0 = int(ty) * BYI, zb = int(tz) * a.zc;
   const int ze = min(zb + a.zc, nz);
