@@ -365,11 +365,11 @@ lbm_status lbm_get_step(const lbm_lattice *L, unsigned long long *steps);
  * node per thread with a solid mask, face field or geometry; each XCD
  * placement) one untimed and trial_steps >= 1 timed steps, and, in the
  * row-major layout without those options, for each two-step pass
- * (lbm_set_steps_per_pass: z ranges of 16, 32 or 64 planes, tiles of the
- * form's default rows, 5 or 12 rows (FP64: its 7 only), slab or
- * dispatch-order placement) one
- * untimed and trial_steps timed pairs, on the lattice's stream (HIP events,
- * compared per step).  The steps are part of the run (results do not depend
+ * (lbm_set_steps_per_pass: z ranges of 16 and 32 planes and one that fills
+ * the device's compute units, or 64, tiles of the form's default rows, 5 or
+ * 12 rows (FP64: its 7 only), slab or dispatch-order placement) one untimed
+ * and trial_steps timed pairs, on the lattice's stream (HIP events, compared
+ * per step).  The steps are part of the run (results do not depend
  * on the choice).  Sets the winner -- launch shape, steps per pass, z range
  * and tile rows -- and returns the launch shape through the non-NULL
  * pointers (lbm_get_steps_per_pass gives the rest).  Synchronizes.  Errors:

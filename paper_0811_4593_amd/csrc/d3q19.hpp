@@ -82,16 +82,24 @@ __device__ __forceinline__ T quotient(T a, T den, T inv) {
   return fused_add(fused_add(-den, q, a), inv, q);
 }
 
+// Unit of the update's arithmetic: it works on unit<T>() times the
+// deviations (and densities): 2^8 in float, the arithmetic of the FP16 forms,
+// which store that number.
+template <class T>
+__host__ __device__ constexpr T unit() {
+  return sizeof(T) == 4 ? T(256) : T(1);
+}
+
 // Per-lattice parameters of the node update.
 template <class T>
 struct NodeParams {
   unsigned bc_mask;  // bit f: face f is bounded (velocity or pressure BC)
   unsigned p_mask;   // bit f: face f is a pressure face (subset of bc_mask)
   T omega;           // 1 / tau
-  T tau_f[3];        // tau * F: velocity shift times rho inside f^eq (body force F)
+  T tau_f[3];        // tau * F: velocity shift times rho inside f^eq (body force F), in unit<T>()
   FaceVel<T> fv;     // velocity faces: the velocity; pressure faces: the
                      // tangential velocity (normal component zero)
-  T rho_p[6];        // prescribed density of each pressure face
+  T rho_p[6];        // prescribed density of each pressure face, in unit<T>()
   T den[6], inv[6];  // divisor of the face's bracket, 1 - v.n (velocity face)
                      // or rho_p (pressure face), and its reciprocal
   unsigned rule_flags;  // kRuleNoTransverse: face rule without the corrections N
@@ -108,7 +116,7 @@ __device__ __forceinline__ void face_values(unsigned m, const NodeParams<T> &p, 
   vx = T(0);
   vy = T(0);
   vz = T(0);
-  r0 = T(1);
+  r0 = unit<T>();
 #pragma unroll
   for (int b = 0; b < 6; ++b)
     if (m == (1u << b)) {
@@ -182,7 +190,7 @@ __device__ __forceinline__ void face_values(unsigned m, const NodeParams<T> &p, 
 // Values of one face.
 template <class T>
 struct FaceVals {
-  T v[3], r0;   // velocity or tangential velocity, prescribed density
+  T v[3], r0;   // velocity or tangential velocity, prescribed density (in unit<T>())
   T den, inv;   // as NodeParams
 };
 
@@ -214,7 +222,7 @@ __device__ __forceinline__ void face_rule(T (&d)[19], bool mine, bool pressure, 
       for (int a = 0; a < 3; ++a)
         if (c[a]) M[a] += T(c[a]) * d[k];
   }
-  const T B = T(1) + s_known + s_out;
+  const T B = unit<T>() + s_known + s_out;
   const T q = quotient(B, f.den, f.inv);
   T v[3] = {f.v[0], f.v[1], f.v[2]}, rho = q;
   if (pressure) {
@@ -289,7 +297,7 @@ __device__ __forceinline__ void edge_corner_rule(T (&d)[19], bool mine, unsigned
   for (int k = 0; k < 18; ++k) s += ((bur >> k) & 1u) ? T(0) : d[k];
   T db = quotient(s, edge ? T(22) : T(18), edge ? T(1) / T(22) : T(1) / T(18));
   if (__builtin_amdgcn_ballot_w64(pressure)) {
-    const T db_p = quotient(r0 - T(1) - s, edge ? T(14) : T(18), edge ? T(1) / T(14) : T(1) / T(18));
+    const T db_p = quotient(r0 - unit<T>() - s, edge ? T(14) : T(18), edge ? T(1) / T(14) : T(1) / T(18));
     db = pressure ? db_p : db;
   }
 #pragma unroll
@@ -326,7 +334,7 @@ __device__ __forceinline__ void apply_boundary_rule(T (&d)[19], unsigned m, unsi
 // Density of the pressure face among the faces pm (at most one bit).
 template <class T, class Rho>
 __device__ __forceinline__ T edge_density(unsigned pm, const Rho &rho) {
-  T r0 = T(1);
+  T r0 = unit<T>();
 #pragma unroll
   for (int b = 0; b < 6; ++b)
     if (pm & (1u << b)) r0 = rho(b);
@@ -490,7 +498,7 @@ __device__ __forceinline__ void bgk_collide(T (&d)[19], T omega, const T (&tau_f
     if (cz(k) < 0) zm += d[k];
   }
   const T drho = (xp + xm) + x0;
-  const T rho = T(1) + drho;
+  const T rho = unit<T>() + drho;
   // 1 / rho: correctly rounded in double; in float (the FP16 forms, whose
   // storage keeps 11 bits) the hardware reciprocal, within about 1 ulp, in
   // one instruction instead of the ten of a rounded division

@@ -95,12 +95,12 @@ __device__ __forceinline__ NodeParams<T> lattice_params(const BatchLat &L) {
   prm.omega = T(L.omega);
 #pragma unroll
   for (int f = 0; f < 6; ++f) {
-    prm.rho_p[f] = T(L.rho_p[f]);
+    prm.rho_p[f] = unit<T>() * T(L.rho_p[f]);
     prm.den[f] = T(L.den[f]);
     prm.inv[f] = T(L.inv[f]);
   }
 #pragma unroll
-  for (int d = 0; d < 3; ++d) prm.tau_f[d] = T(L.tau_f[d]);
+  for (int d = 0; d < 3; ++d) prm.tau_f[d] = unit<T>() * T(L.tau_f[d]);
 #pragma unroll
   for (int f = 0; f < 6; ++f)
 #pragma unroll
@@ -368,16 +368,6 @@ static hipError_t launch_batch_sweep(int storage, int bx, const BatchLat *lats, 
   return hipGetLastError();
 }
 
-// Interior rows of the two-step pass's tiles for a storage form.
-static int pass_rows(int storage) {
-  switch (storage) {
-    case kStoreF64: return Sweep2Rows<FormF64>::kBYI;
-    case kStoreF32: return Sweep2Rows<FormF32>::kBYI;
-    case kStoreF16: return Sweep2Rows<FormF16>::kBYI;
-    default: return Sweep2Rows<FormF16SR>::kBYI;
-  }
-}
-
 template <class F>
 static void launch_batch_pass_t(const BatchLat *lats, const BatchBox *boxes, const int *nb, int s, int parity, int zc,
                                 int remap, int grid, hipStream_t st) {
@@ -405,7 +395,7 @@ static void set_lattice_divisors(BatchLat &L) {
   NodeParams<T> p;
   p.p_mask = L.p_mask;
   for (int f = 0; f < 6; ++f) {
-    p.rho_p[f] = T(L.rho_p[f]);
+    p.rho_p[f] = unit<T>() * T(L.rho_p[f]);
     for (int d = 0; d < 3; ++d) p.fv.v[f][d] = T(L.v[f][d]);
   }
   set_face_divisors<T>(p);
@@ -798,7 +788,7 @@ lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) 
         return bfail(LBM_ERR_STATE, "job %d is not row-major: two steps per pass need every job row-major",
                      B->slot_job[slot]);
       // boxes z range by z range, row of tiles by row of tiles
-      const unsigned by = unsigned(lbm::pass_rows(st)), zc = unsigned(B->pass_zc);
+      const unsigned by = unsigned(lbm::sweep2_rows(st, 0)), zc = unsigned(B->pass_zc);
       const unsigned tx = (unsigned(J.spec.nx) + 63u) / 64u, ty = (unsigned(J.spec.ny) + by - 1u) / by;
       const unsigned tz = (unsigned(J.spec.nz) + zc - 1u) / zc;
       for (unsigned z = 0; z < tz; ++z)

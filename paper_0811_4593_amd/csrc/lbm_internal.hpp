@@ -109,6 +109,8 @@ size_t sweep_delta_partials(const SweepConfig &c);
 // of one population), a z plane's bytes within the 32-bit offsets of a buffer
 // descriptor.
 bool sweep2_takes(const PopLayout &lay, int ny, int storage);
+// Interior rows of the pass's tiles for a storage form and tile_rows (0, 5 or 12).
+int sweep2_rows(int storage, int tile_rows);
 hipError_t launch_sweep2(const SweepConfig &c, int zc, int rows, const void *src, void *dst, hipStream_t s);
 
 // Node codes of a complex geometry from node types (0 fluid, 1 wall node,

@@ -332,9 +332,9 @@ static SweepArgs<T> make_args(const SweepConfig &c) {
   a.ext.solid = c.solid;
   a.ext.code = c.geo_code;
   for (int f = 0; f < 6; ++f) a.ext.face_v[f] = c.face_v[f];
-  for (int f = 0; f < 6; ++f) a.p.rho_p[f] = T(c.rho_p[f]);
+  for (int f = 0; f < 6; ++f) a.p.rho_p[f] = unit<T>() * T(c.rho_p[f]);
   a.p.omega = T(1.0 / c.tau);
-  for (int d = 0; d < 3; ++d) a.p.tau_f[d] = T(c.tau * c.force[d]);
+  for (int d = 0; d < 3; ++d) a.p.tau_f[d] = unit<T>() * T(c.tau * c.force[d]);
   a.key = step_key(c.step);
   for (int f = 0; f < 6; ++f)
     for (int d = 0; d < 3; ++d) a.p.fv.v[f][d] = T(c.v[f][d]);

@@ -59,8 +59,8 @@ static hipError_t launch_sweep2_t(const SweepConfig &c, int zc, const void *src,
   a.p.p_mask = c.p_mask;
   a.p.rule_flags = c.rule_flags;
   a.p.omega = T(1.0 / c.tau);
-  for (int d = 0; d < 3; ++d) a.p.tau_f[d] = T(c.tau * c.force[d]);
-  for (int f = 0; f < 6; ++f) a.p.rho_p[f] = T(c.rho_p[f]);
+  for (int d = 0; d < 3; ++d) a.p.tau_f[d] = unit<T>() * T(c.tau * c.force[d]);
+  for (int f = 0; f < 6; ++f) a.p.rho_p[f] = unit<T>() * T(c.rho_p[f]);
   for (int f = 0; f < 6; ++f)
     for (int d = 0; d < 3; ++d) a.p.fv.v[f][d] = T(c.v[f][d]);
   set_face_divisors<T>(a.p);
@@ -75,6 +75,15 @@ static hipError_t launch_sweep2_t(const SweepConfig &c, int zc, const void *src,
 bool sweep2_takes(const PopLayout &lay, int ny, int storage) {
   const size_t esize = storage == kStoreF64 ? 8 : (storage == kStoreF32 ? 4 : 2);
   return lay.row_stride == 19 * lay.pop_stride && lay.row_stride * esize * size_t(ny) < (size_t(1) << 32);
+}
+
+int sweep2_rows(int storage, int tile_rows) {
+  switch (storage) {
+    case kStoreF64: return Sweep2Rows<FormF64>::kBYI;
+    case kStoreF32: return tile_rows ? tile_rows : Sweep2Rows<FormF32>::kBYI;
+    case kStoreF16: return tile_rows ? tile_rows : Sweep2Rows<FormF16>::kBYI;
+    default: return tile_rows ? tile_rows : Sweep2Rows<FormF16SR>::kBYI;
+  }
 }
 
 hipError_t launch_sweep2(const SweepConfig &c, int zc, int rows, const void *src, void *dst, hipStream_t s) {

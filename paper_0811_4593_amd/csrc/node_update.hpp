@@ -17,6 +17,12 @@ namespace lbm {
 // quantity is the deviation d_k = f_k - w_k from the rest state (w_k: lattice
 // weight); the FP16 form stores it scaled, h = RNE(d * 2^8), d = h * 2^-8
 // (exact scaling).
+//
+// decode / encode: the deviation d.  load / store: the deviation in the unit
+// of the update's arithmetic, unit<T>() * d.  For the FP16 forms that is the
+// stored number itself: the rules and the collision are homogeneous in the
+// populations, so with their constants scaled by 2^8 too they give 2^8 times
+// the result, bit for bit, without 38 multiplications a node.
 // ---------------------------------------------------------------------------
 template <class S>
 struct Codec;
@@ -26,6 +32,8 @@ struct Codec<double> {
   using T = double;
   static __device__ __forceinline__ T decode(double s) { return s; }
   static __device__ __forceinline__ double encode(T v) { return v; }
+  static __device__ __forceinline__ T load(double s) { return s; }
+  static __device__ __forceinline__ double store(T v) { return v; }
 };
 
 // FP32 storage is updated in double: the per-step rounding of the arithmetic
@@ -37,6 +45,8 @@ struct Codec<float> {
   using T = double;
   static __device__ __forceinline__ T decode(float s) { return double(s); }
   static __device__ __forceinline__ float encode(T v) { return float(v); }
+  static __device__ __forceinline__ T load(float s) { return double(s); }
+  static __device__ __forceinline__ float store(T v) { return float(v); }
 };
 
 template <>
@@ -44,6 +54,8 @@ struct Codec<_Float16> {
   using T = float;
   static __device__ __forceinline__ T decode(_Float16 s) { return static_cast<float>(s) * 0.00390625f; }
   static __device__ __forceinline__ _Float16 encode(T v) { return static_cast<_Float16>(v * 256.0f); }
+  static __device__ __forceinline__ T load(_Float16 s) { return static_cast<float>(s); }
+  static __device__ __forceinline__ _Float16 store(T v) { return static_cast<_Float16>(v); }
 };
 
 // Storage forms of the sweep: element type S, arithmetic type T and how the
@@ -85,29 +97,29 @@ __host__ __device__ __forceinline__ unsigned fmix32(unsigned h) {
 // Key of time step t for the stochastic rounding.
 __host__ __device__ __forceinline__ unsigned step_key(unsigned t) { return fmix32(t * 0x9e3779b1u + 0x7f4a7c15u); }
 
-// d * 2^8 rounded stochastically to half precision; r: 32 random bits.
-// gfx950's conversion with stochastic rounding adds the top 13 bits of r
+// v (the deviation times 2^8) rounded stochastically to half precision; r: 32
+// random bits.  gfx950's conversion with stochastic rounding adds the top 13 bits of r
 // below the half-precision cut of the float before truncating (for a normal
 // float a = e<<23 | m that is ((a - 0x38000000) + (r >> 19)) >> 13), so it
-// rounds up with probability (m mod 2^13) / 2^13 and E[h] = d * 2^8; a carry
+// rounds up with probability (m mod 2^13) / 2^13 and E[h] = v; a carry
 // out of the mantissa moves to the next binade, and half subnormals are
 // rounded the same way.
-__device__ __forceinline__ _Float16 encode_half_sr(float d, unsigned r) {
+__device__ __forceinline__ _Float16 store_half_sr(float v_in, unsigned r) {
   typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
   // The conversion writes the low half and keeps the high half of its
   // destination; only the low half is used, so the destination starts as
   // the random word itself rather than a zeroed register.
   half2_t v = __builtin_bit_cast(half2_t, r);
-  v = __builtin_amdgcn_cvt_sr_f16_f32(v, d * 256.0f, r, false);
+  v = __builtin_amdgcn_cvt_sr_f16_f32(v, v_in, r, false);
   return v[0];
 }
 
 template <class F>
-__device__ __forceinline__ typename F::S encode_form(typename Codec<typename F::S>::T v, unsigned r) {
+__device__ __forceinline__ typename F::S store_form(typename Codec<typename F::S>::T v, unsigned r) {
   if constexpr (F::kStochastic)
-    return encode_half_sr(v, r);
+    return store_half_sr(v, r);
   else
-    return Codec<typename F::S>::encode(v);
+    return Codec<typename F::S>::store(v);
 }
 
 // Pointer into global memory.  Kernels whose buffer addresses come from
@@ -431,7 +443,7 @@ __device__ __forceinline__ void update_node(const Access &mem, const NodeGeom &g
   if (!COPY && !solid_node) {
     T f[19];
 #pragma unroll
-    for (int k = 0; k < 19; ++k) f[k] = Codec<S>::decode(raw[k]);
+    for (int k = 0; k < 19; ++k) f[k] = Codec<S>::load(raw[k]);
     unsigned m = 0;
     if (x == 0) m |= bc_mask & 1u;
     if (unsigned(x) == nx - 1) m |= bc_mask & 2u;
@@ -443,7 +455,7 @@ __device__ __forceinline__ void update_node(const Access &mem, const NodeGeom &g
       // Complex geometry: walls at rest, rule from the node code.
       const unsigned kind = gcode >> 24;
       if (kind == kGeoPlaneEdgeCorner) {
-        boundary_rule<T>(f, (gcode >> 18) & 63u, p, 0u, T(0), T(0), T(0), T(1));
+        boundary_rule<T>(f, (gcode >> 18) & 63u, p, 0u, T(0), T(0), T(0), unit<T>());
       } else if (kind == kGeoConvexEdge) {
         convex_edge_rule<T>(f, gcode & 0x3ffffu);
       } else if (kind == kGeoGeneral) {
@@ -475,7 +487,7 @@ __device__ __forceinline__ void update_node(const Access &mem, const NodeGeom &g
     // only its top 13 bits are used).
     const unsigned r0 = F::kStochastic ? fmix32(n * 0x9e3779b1u + key) : 0u;
 #pragma unroll
-    for (int k = 0; k < 19; ++k) raw[k] = encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
+    for (int k = 0; k < 19; ++k) raw[k] = store_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
   }
 #pragma unroll
   for (int k = 0; k < 19; ++k) mem.store_at(k, row, unsigned(x), raw[k]);

@@ -190,7 +190,7 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
     const int s3_2 = s3 == 2 ? 0 : s3 + 1;  // slot of two rounds back (p - 2 = p + 1 mod 3)
     T f[19];
 #pragma unroll
-    for (int k = 0; k < 19; ++k) f[k] = Codec<S>::decode(raw[k]);
+    for (int k = 0; k < 19; ++k) f[k] = Codec<S>::load(raw[k]);
     complete(f);
     zp = zp == nz - 1 ? 0 : zp + 1;
     plane[2] = plane[1];
@@ -206,7 +206,7 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
       const unsigned r0 = F::kStochastic ? fmix32((nxy + unsigned(z1) * nplane) * 0x9e3779b1u + a.key0) : 0u;
       S e[19];
 #pragma unroll
-      for (int k = 0; k < 19; ++k) e[k] = encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
+      for (int k = 0; k < 19; ++k) e[k] = store_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
       complete(e);
       if (live1) {
 #pragma unroll
@@ -228,11 +228,11 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
 #pragma unroll
       for (int k = 0; k < 19; ++k) {
         if (own_column(k)) {
-          f[k] = Codec<S>::decode(k == 18 ? e18 : (k == 4 ? e4_before : e5));
+          f[k] = Codec<S>::load(k == 18 ? e18 : (k == 4 ? e4_before : e5));
           continue;
         }
         const int slot = cz(k) < 0 ? 0 : (cz(k) == 0 ? 1 - s2 : s3_2);
-        f[k] = Codec<S>::decode((low + slot * ring_slot_planes(cz(k)) * PLANE)[
+        f[k] = Codec<S>::load((low + slot * ring_slot_planes(cz(k)) * PLANE)[
             (ring_first(cz(k)) + ring_rank(k)) * PLANE + (1 - cy(k)) * HX + (1 - cx(k))]);
       }
       const unsigned m = mxy | (z2 == 0 ? a.p.bc_mask & 16u : 0u) | (z2 == nz - 1 ? a.p.bc_mask & 32u : 0u);
@@ -242,7 +242,7 @@ __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, 
       const unsigned r0 = F::kStochastic ? fmix32((nxy + unsigned(z2) * nplane) * 0x9e3779b1u + a.key1) : 0u;
       S e[19];
 #pragma unroll
-      for (int k = 0; k < 19; ++k) e[k] = encode_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
+      for (int k = 0; k < 19; ++k) e[k] = store_form<F>(f[k], r0 + unsigned(k + 1) * 0x9e3779b9u);
       complete(e);
       wait_loads();
       if (live1) {
