@@ -449,6 +449,7 @@ static lbm::SweepConfig sweep_config(const lbm_lattice *L) {
   c.rule_flags = L->rule_flags;
   c.solid = L->d_solid;
   c.geo_code = L->d_geo;
+  c.solids_kept = false;
   for (int f = 0; f < 6; ++f) c.face_v[f] = L->d_face_v[f];
   c.block_x = L->block_x;
   c.nodes_per_thread = L->npt;
@@ -478,6 +479,7 @@ lbm_status lbm_step(lbm_lattice *L, int nsteps) {
   const bool two = L->pass_steps == 2 && lbm::sweep2_takes(L->lay, L->ny, L->storage) && !ext;
   for (int s = 0; s < nsteps;) {
     c.step = unsigned(L->steps);
+    c.solids_kept = s > 0;  // copied by the first step of this call
     const bool pair = two && nsteps - s >= 2;
     hipError_t e = pair ? lbm::launch_sweep2(c, L->zc, L->tile_rows, L->buf[L->cur], L->buf[L->cur ^ 1], L->stream)
                         : lbm::launch_sweep(c, L->buf[L->cur], L->buf[L->cur ^ 1], false, L->stream);

@@ -73,6 +73,7 @@ struct SweepConfig {
   const unsigned *solid;             // device [N] solid words (NodeExt), or nullptr
   const double *face_v[6];           // device per-node face velocities, or nullptr
   const unsigned *geo_code;          // device complex-geometry node codes, or nullptr
+  bool solids_kept;                  // NodeExt::solids_kept
   int block_x;
   int nodes_per_thread;
   int xcd_remap;

@@ -331,6 +331,7 @@ static SweepArgs<T> make_args(const SweepConfig &c) {
   a.p.rule_flags = c.rule_flags;
   a.ext.solid = c.solid;
   a.ext.code = c.geo_code;
+  a.ext.solids_kept = c.solids_kept;
   for (int f = 0; f < 6; ++f) a.ext.face_v[f] = c.face_v[f];
   for (int f = 0; f < 6; ++f) a.p.rho_p[f] = unit<T>() * T(c.rho_p[f]);
   a.p.omega = T(1.0 / c.tau);

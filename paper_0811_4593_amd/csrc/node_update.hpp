@@ -349,6 +349,7 @@ struct NodeExt {
                                // order: x faces y + ny z, y faces x + nx z,
                                // z faces x + nx y
   const unsigned *code;        // [N] complex-geometry node codes, or nullptr
+  bool solids_kept;            // the destination already holds the solid nodes' populations
 };
 
 // Solid word of a node of a lattice with a solid mask (built on the host):
@@ -406,8 +407,21 @@ __device__ __forceinline__ void update_node(const Access &mem, const NodeGeom &g
       solid_node = (gcode >> 24) == kGeoSolid;
     }
   }
+  // A solid node (or solid interior of a geometry) keeps its populations.  The
+  // second buffer holds them too once a step of the same run has copied them;
+  // the later steps then leave a cache line's nodes alone if all of them are
+  // solid (skipping single nodes would write the others' lines in parts: 1.26
+  // times slower on a channel with ribs).  On the 256 x 32 x 512 FP32 tilted
+  // channel, 69% solid, a step took 109 us with the copies, 60 us without.
+  if constexpr (EXT) {
+    if (ext.solids_kept) {
+      constexpr unsigned kLine = 128 / sizeof(S);  // nodes of a line: 16, 32 or 64
+      const unsigned long long fluid = __builtin_amdgcn_ballot_w64(!solid_node);
+      const unsigned first = (threadIdx.x & 63u) & ~(kLine - 1u);
+      if (((fluid >> first) & (~0ull >> (64u - kLine))) == 0ull) return;
+    }
+  }
   if (EXT && solid_node) {
-    // a solid node (or solid interior of a geometry) keeps its populations
 #pragma unroll
     for (int k = 0; k < 19; ++k) raw[k] = mem.load_at(k, row, unsigned(x));
   } else if (EXT && ext.solid) {
