@@ -349,7 +349,11 @@ lbm_status lbm_get_launch(const lbm_lattice *L, int *block_x, int *nodes_per_thr
  * measured faster than 13 rows on 512 x 256 x 256 FP32, slower on
  * 1024 x 512 x 512); FP64 tiles have seven rows either way.  Every variant
  * gives the same bits.  steps_per_pass = 1: one single sweep per step (the
- * default).  Errors: LBM_ERR_ARG (NULL, steps_per_pass not 1 or 2,
+ * default); small lattices (up to about 65000 nodes, without those options)
+ * make two or three steps per launch, and until this call, lbm_set_launch or
+ * lbm_autotune chooses the launch, larger row-major ones make passes where
+ * they are estimated to be faster -- with the same bits, in the buffer that
+ * single steps end in.  Errors: LBM_ERR_ARG (NULL, steps_per_pass not 1 or 2,
  * z_planes < 0, tile_rows not 0, 5 or 12). */
 lbm_status lbm_set_steps_per_pass(lbm_lattice *L, int steps_per_pass, int z_planes, int tile_rows);
 lbm_status lbm_get_steps_per_pass(const lbm_lattice *L, int *steps_per_pass, int *z_planes, int *tile_rows);
@@ -536,7 +540,8 @@ lbm_status lbm_batch_get_shape(const lbm_batch *B, int *block_x, int *tile_nodes
 
 /* Steps per pass over HBM for the batch's chunks (Sec. II's update, two steps
  * at a time as lbm_set_steps_per_pass does for one lattice):
- *   1 (the default)  one step per launch;
+ *   1 (the default)  one step per launch, except that until this call a chunk
+ *                    of one job is grouped as lbm_step groups its steps;
  *   2                every chunk by passes of two steps: one launch per
  *                    storage form over the 64 x 13 (FP64: 64 x 7) tiles and
  *                    z ranges of z_planes planes (0: 32) of all its jobs, or

@@ -649,6 +649,7 @@ struct lbm_batch {
   // jobs of every chunk (every job row-major), z ranges of pass_zc planes per
   // workgroup, box order pass_remap on the XCDs.
   int pass_steps = 1, pass_zc = 32, pass_remap = 1;
+  bool pass_auto = true;  // lbm_batch_set_steps_per_pass has not been called
   std::map<int, Job> jobs;
   std::deque<int> queue;
   std::vector<int> slot_job;           // slot -> job id (-1 free)
@@ -896,22 +897,41 @@ bool measured_in_last_step(const lbm_batch *B, bool solo) {
 }
 
 // A chunk that steps a single job: plain launches of the single-lattice
-// sweep on the job's buffers (row-aligned blocks; bitwise the batch sweep's
-// results), one per step, each with the job's own step index; the last one
-// also takes the convergence measure.
+// kernels on the job's buffers (row-aligned blocks; bitwise the batch sweep's
+// results), each with the job's own step index.  First launches of several
+// steps: passes with two steps per pass set; otherwise, unless one step per
+// pass was asked for, as lbm_step does -- blocks of steps for a small job,
+// passes for a larger one where they pay.  Then single steps, of which the
+// last also takes the convergence measure.  Launches of two steps come in
+// pairs, so that the chunk ends in buf[0] (launches of three do not change
+// the parity).
 lbm_status run_solo_chunk(lbm_batch *B, Lane &ln, int slot) {
   const Job &J = B->jobs.at(B->slot_job[slot]);
   const lbm::BatchLat &L = B->lat[slot];
   lbm::SweepConfig c = J.cfg;
-  // with two steps per pass, passes of the single-lattice two-step kernel
-  // first (the same order of buffers as launch_steps; the job is row-major)
-  const int P = B->pass_steps == 2 ? passes_in(B->chunk_steps) : 0;
-  for (int i = 0; i < P; ++i) {
-    c.step = unsigned(J.steps + 2 * i);
-    LBM_BHIP(lbm::launch_sweep2(c, B->pass_zc, 0, L.buf[i & 1], L.buf[(i & 1) ^ 1], ln.stream), "pass launch");
+  int per = 0, launches = 0, zc = 0;  // steps per launch, launches, z range of a pass (0: blocks)
+  if (B->pass_steps == 2) {
+    per = 2;
+    launches = passes_in(B->chunk_steps);
+    zc = B->pass_zc;
+  } else if (B->pass_auto) {
+    per = lbm::block_steps(c);
+    if (per == 0) {
+      zc = lbm::sweep2_pays(c, B->num_cu);
+      per = zc > 0 ? 2 : 0;
+    }
+    if (per > 0) launches = (B->chunk_steps - 1) / per;
+    if (per == 2) launches &= ~1;
   }
-  for (int s = 2 * P; s < B->chunk_steps; ++s) {
-    const int q = (s - P) & 1;
+  for (int i = 0; i < launches; ++i) {
+    c.step = unsigned(J.steps + per * i);
+    const void *from = L.buf[i & 1];
+    void *to = L.buf[(i & 1) ^ 1];
+    LBM_BHIP(zc > 0 ? lbm::launch_sweep2(c, zc, 0, from, to, ln.stream) : lbm::launch_block_steps(c, from, to, ln.stream),
+             "launch of several steps");
+  }
+  for (int s = per * launches; s < B->chunk_steps; ++s) {
+    const int q = (s - per * launches + launches) & 1;
     c.step = unsigned(J.steps + s);
     if (s == B->chunk_steps - 1 && measured_in_last_step(B, true)) {
       lbm_status st = ensure_partials(ln, lbm::sweep_delta_partials(c));
@@ -1568,6 +1588,7 @@ lbm_status lbm_batch_set_steps_per_pass(lbm_batch *B, int steps_per_pass, int z_
           kv.second.layout != LBM_LAYOUT_ROW_MAJOR)
         return bfail(LBM_ERR_STATE, "job %d is stored population-major: two steps per pass need row-major jobs "
                      "(set the mode before submitting)", kv.first);
+  B->pass_auto = false;
   B->pass_steps = steps_per_pass;
   B->pass_zc = z_planes == 0 ? 32 : z_planes;
   return LBM_OK;

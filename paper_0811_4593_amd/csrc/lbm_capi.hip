@@ -20,6 +20,16 @@ thread_local char g_err[512] = "";
 
 }  // namespace
 
+int lbm::device_compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) {
+    (void)hipGetLastError();
+    return 256;
+  }
+  return n;
+}
+
 lbm_status lbm::set_error(lbm_status st, const char *fmt, ...) {
   va_list ap;
   va_start(ap, fmt);
@@ -73,6 +83,8 @@ struct lbm_lattice {
   unsigned *d_geo;         // complex-geometry node codes on the device, or nullptr
   int block_x, npt, xcd;
   int pass_steps;  // 1 or 2 steps per pass over HBM
+  bool pass_auto;  // neither the steps per pass nor the launch shape chosen by the caller or lbm_autotune
+  int compute_units;
   int zc;          // z-planes per workgroup of the two-step pass
   int tile_rows;   // interior rows of its tiles (0: the form's default)
   unsigned long long steps;  // steps taken since creation (its low 32 bits key the stochastic rounding)
@@ -129,6 +141,8 @@ static void default_launch(lbm_lattice *L) {
   L->pass_steps = 1;
   L->zc = kDefaultZPlanes;
   L->tile_rows = 0;
+  L->pass_auto = true;
+  L->compute_units = lbm::device_compute_units();
 }
 
 static lbm_status finish_create(lbm_lattice *L, double rho0, const double u0[3], lbm_lattice **out) {
@@ -477,16 +491,31 @@ lbm_status lbm_step(lbm_lattice *L, int nsteps) {
   const bool ext = L->d_solid || L->d_geo || L->d_face_v[0] || L->d_face_v[1] || L->d_face_v[2] ||
                    L->d_face_v[3] || L->d_face_v[4] || L->d_face_v[5];
   const bool two = L->pass_steps == 2 && lbm::sweep2_takes(L->lay, L->ny, L->storage) && !ext;
+  // With one step per pass: small lattices by blocks of steps, and, as long as
+  // the caller has chosen no launch, larger ones by passes where they pay.
+  // Launches of an even number of steps then come in pairs, so that the state
+  // alternates between the buffers as with single steps.
+  const int block = L->pass_steps == 1 && !ext ? lbm::block_steps(c) : 0;
+  const int auto_zc = L->pass_steps == 1 && !ext && block == 0 && L->pass_auto && nsteps >= 4
+                          ? lbm::sweep2_pays(c, L->compute_units)
+                          : 0;
+  const int group = two || auto_zc > 0 ? 2 : block;
+  int groups = group > 0 ? nsteps / group : 0;  // launches of `group` steps; then single steps
+  if (!two && group == 2) groups &= ~1;
   for (int s = 0; s < nsteps;) {
     c.step = unsigned(L->steps);
     c.solids_kept = s > 0;  // copied by the first step of this call
-    const bool pair = two && nsteps - s >= 2;
-    hipError_t e = pair ? lbm::launch_sweep2(c, L->zc, L->tile_rows, L->buf[L->cur], L->buf[L->cur ^ 1], L->stream)
-                        : lbm::launch_sweep(c, L->buf[L->cur], L->buf[L->cur ^ 1], false, L->stream);
-    if (e != hipSuccess) return hip_fail(e, pair ? "two-step sweep launch" : "sweep launch");
+    const int n = groups-- > 0 ? group : 1;
+    const void *from = L->buf[L->cur];
+    void *to = L->buf[L->cur ^ 1];
+    const hipError_t e = n == 1   ? lbm::launch_sweep(c, from, to, false, L->stream)
+                         : two    ? lbm::launch_sweep2(c, L->zc, L->tile_rows, from, to, L->stream)
+                         : auto_zc > 0 ? lbm::launch_sweep2(c, auto_zc, 0, from, to, L->stream)
+                                  : lbm::launch_block_steps(c, from, to, L->stream);
+    if (e != hipSuccess) return hip_fail(e, n == 1 ? "sweep launch" : "launch of several steps");
     L->cur ^= 1;
-    L->steps += pair ? 2 : 1;
-    s += pair ? 2 : 1;
+    L->steps += unsigned(n);
+    s += n;
   }
   return LBM_OK;
 }
@@ -625,6 +654,7 @@ lbm_status lbm_set_launch(lbm_lattice *L, int block_x, int nodes_per_thread, int
   L->block_x = block_x;
   L->npt = nodes_per_thread;
   L->xcd = xcd_remap;
+  L->pass_auto = false;
   return LBM_OK;
 }
 
@@ -643,6 +673,7 @@ lbm_status lbm_set_steps_per_pass(lbm_lattice *L, int steps_per_pass, int z_plan
   if (z_planes < 0) return fail(LBM_ERR_ARG, "z_planes must be >= 0 (got %d)", z_planes);
   if (tile_rows != 0 && tile_rows != 5 && tile_rows != 12)
     return fail(LBM_ERR_ARG, "tile_rows must be 0, 5 or 12 (got %d)", tile_rows);
+  L->pass_auto = false;
   L->pass_steps = steps_per_pass;
   L->zc = z_planes == 0 ? kDefaultZPlanes : z_planes;
   L->tile_rows = tile_rows;
@@ -669,17 +700,6 @@ lbm_status lbm_get_step(const lbm_lattice *L, unsigned long long *steps) {
   if (!L || !steps) return fail(LBM_ERR_ARG, "NULL argument");
   *steps = L->steps;
   return LBM_OK;
-}
-
-// Compute units of the current device (256 if it cannot be asked).
-static int compute_units() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) {
-    (void)hipGetLastError();
-    return 256;
-  }
-  return n;
 }
 
 lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *nodes_per_thread, int *xcd_remap) {
@@ -712,26 +732,23 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
   if (lbm::sweep2_takes(L->lay, L->ny, L->storage) && !ext)
     for (int rows : {0, 5, 12}) {
       if (rows != 0 && L->storage == LBM_STORE_F64) continue;  // FP64 tiles have 7 rows either way
-      // z ranges of 16 and 32 planes, and the one that gives every compute
-      // unit of the device one workgroup (or two, or 64 planes where that
-      // range is longer or one of the two): a lattice of a few million nodes
-      // has only a few hundred workgroups, and 200 x 100 x 100 FP32 takes
-      // 0.054 ms per step with 13 planes (256 workgroups), 0.075 with 16.
-      int zcs[3] = {16, 32, 64};
-      const int by = lbm::sweep2_rows(L->storage, rows);
-      const long layer = long((L->nx + 63) / 64) * ((L->ny + by - 1) / by);
-      for (long round = 2; round >= 1; --round) {
-        const long ranges = round * compute_units() * (rows == 5 ? 2 : 1) / layer;
-        const int zc = ranges > 0 ? int((L->nz + ranges - 1) / ranges) : 64;
-        if (zc < 64 && zc != 16 && zc != 32) zcs[2] = zc;
-      }
+      // z ranges of 16 and 32 planes, and the one estimated best for the
+      // lattice's size (64 planes if that is one of the two): a lattice of a
+      // few million nodes has only a few hundred workgroups, and 200 x 100 x
+      // 100 FP32 takes 0.054 ms per step with 13 planes (256 workgroups),
+      // 0.075 with 16.
+      const int zc_best = lbm::sweep2_plan(sweep_config(L), rows, L->compute_units).zc;
+      const int zcs[3] = {16, 32, zc_best > 0 && zc_best != 16 && zc_best != 32 ? zc_best : 64};
       for (int zc : zcs)
         for (int xcd : {LBM_XCD_SLABS, LBM_XCD_NONE}) cands.push_back({2, L->block_x, L->npt, xcd, zc, rows});
     }
+  const bool old_auto = L->pass_auto;
+  L->pass_auto = false;
   const int old[6] = {L->block_x, L->npt, L->xcd, L->pass_steps, L->zc, L->tile_rows};
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     if (e0) (void)hipEventDestroy(e0);
+    L->pass_auto = old_auto;
     return hip_fail(hipGetLastError(), "event creation");
   }
   float best_ms = 0.0f;
@@ -771,6 +788,7 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
     L->pass_steps = old[3];
     L->zc = old[4];
     L->tile_rows = old[5];
+    L->pass_auto = old_auto;
     return result != LBM_OK ? result : fail(LBM_ERR_STATE, "no launch shape to try");
   }
   const Cand &c = cands[best];

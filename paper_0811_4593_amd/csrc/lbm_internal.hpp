@@ -114,6 +114,25 @@ bool sweep2_takes(const PopLayout &lay, int ny, int storage);
 int sweep2_rows(int storage, int tile_rows);
 hipError_t launch_sweep2(const SweepConfig &c, int zc, int rows, const void *src, void *dst, hipStream_t s);
 
+// The z range (planes per workgroup) a pass takes least time with, estimated,
+// and that time; zc 0 for lattices of fewer than four planes.
+struct PassPlan {
+  int zc;
+  double us;
+};
+PassPlan sweep2_plan(const SweepConfig &c, int rows, int compute_units);
+// The z range with which passes are estimated to beat single sweeps by 3% or
+// more on this lattice, or 0.
+int sweep2_pays(const SweepConfig &c, int compute_units);
+// Compute units of the current device (256 if it cannot be asked).
+int device_compute_units();
+
+// Steps one launch_block_steps launch makes on a lattice without solid mask,
+// face field or geometry (c.step and the following), or 0 where single sweeps
+// are faster.
+int block_steps(const SweepConfig &c);
+hipError_t launch_block_steps(const SweepConfig &c, const void *src, void *dst, hipStream_t s);
+
 // Node codes of a complex geometry from node types (0 fluid, 1 wall node,
 // 2 solid interior), all axes periodic; code[n] as geo_code().  Returns the
 // number of nodes of each kind in counts[5] (fluid, solid, plane/edge/corner,

@@ -86,6 +86,42 @@ int sweep2_rows(int storage, int tile_rows) {
   }
 }
 
+// Time of a pass, from what a round takes (one z plane of a workgroup, every
+// compute unit with its own or two small tiles): workgroups run in waves of
+// `slots`, each zc + 2 rounds.  Measured rounds: FP32 6.3 us (1024 x 512 x
+// 512) to 7.5 us (112^3, where every workgroup has boundary nodes), FP64 6.6,
+// FP16 4.9, and 6 us for the launch.
+PassPlan sweep2_plan(const SweepConfig &c, int rows, int compute_units) {
+  const double round_us = c.storage == kStoreF64 ? 6.6 : (c.storage == kStoreF32 ? 7.0 : 4.9);
+  const long slots = long(compute_units) * (rows == 5 ? 2 : 1);
+  const int by = sweep2_rows(c.storage, rows);
+  const long layer = long((c.nx + 63) / 64) * ((c.ny + by - 1) / by);
+  PassPlan best{0, 0.0};
+  const long first = c.nz > 4096 ? (c.nz + 31) / 32 : 1;  // a long axis: 32 planes
+  for (long ranges = first; ranges <= c.nz; ++ranges) {
+    const int zc = int((c.nz + ranges - 1) / ranges);
+    // Longer ranges let neighbouring workgroups drift apart and fetch their
+    // common lines twice (1024 x 512 x 512 FP32: 32 planes 8.4 ms, 64 8.8,
+    // 128 9.0); shorter ones redo too many planes.
+    if (zc > 96) continue;
+    if (zc < 4) break;
+    const long waves = (layer * ((c.nz + zc - 1) / zc) + slots - 1) / slots;
+    const double us = double(waves) * (zc + 2) * round_us * (zc > 48 ? 1.05 : 1.0) + 6.0;
+    if (best.zc == 0 || us < best.us) best = {zc, us};
+    if (first > 1) break;
+  }
+  return best;
+}
+
+// The single sweep moves 2 * 19 elements per node at 5.5 to 6.0 TB/s.
+int sweep2_pays(const SweepConfig &c, int compute_units) {
+  if (!sweep2_takes(c.layout, c.ny, c.storage)) return 0;
+  const double bytes = 38.0 * (c.storage == kStoreF64 ? 8 : (c.storage == kStoreF32 ? 4 : 2)) * c.nx * c.ny * c.nz;
+  const double single_us = bytes / (c.storage == kStoreF64 ? 5.5e6 : (c.storage == kStoreF32 ? 5.6e6 : 6.0e6));
+  const PassPlan p = sweep2_plan(c, 0, compute_units);
+  return p.zc > 0 && p.us < 0.97 * 2.0 * single_us ? p.zc : 0;
+}
+
 hipError_t launch_sweep2(const SweepConfig &c, int zc, int rows, const void *src, void *dst, hipStream_t s) {
   if (!sweep2_takes(c.layout, c.ny, c.storage) || zc < 1) return hipErrorInvalidValue;
   switch (c.storage) {

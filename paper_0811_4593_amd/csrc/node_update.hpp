@@ -55,7 +55,13 @@ struct Codec<_Float16> {
   static __device__ __forceinline__ T decode(_Float16 s) { return static_cast<float>(s) * 0.00390625f; }
   static __device__ __forceinline__ _Float16 encode(T v) { return static_cast<_Float16>(v * 256.0f); }
   static __device__ __forceinline__ T load(_Float16 s) { return static_cast<float>(s); }
-  static __device__ __forceinline__ _Float16 store(T v) { return static_cast<_Float16>(v); }
+  // Rounded to float first, then to half, in every kernel: left to itself the
+  // compiler fuses the rounding to half with the last multiply-add where both
+  // stand in one block (v_fma_mixlo_f16, one rounding) and not elsewhere.
+  static __device__ __forceinline__ _Float16 store(T v) {
+    asm("" : "+v"(v));
+    return static_cast<_Float16>(v);
+  }
 };
 
 // Storage forms of the sweep: element type S, arithmetic type T and how the
@@ -120,6 +126,16 @@ __device__ __forceinline__ typename F::S store_form(typename Codec<typename F::S
     return store_half_sr(v, r);
   else
     return Codec<typename F::S>::store(v);
+}
+
+// Fix the point in the program where a node's 19 values are complete:
+// nothing that computes them moves below.
+template <class V>
+__device__ __forceinline__ void complete(V (&v)[19]) {
+  asm volatile(""
+               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
+                 "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15]),
+                 "+v"(v[16]), "+v"(v[17]), "+v"(v[18]));
 }
 
 // Pointer into global memory.  Kernels whose buffer addresses come from

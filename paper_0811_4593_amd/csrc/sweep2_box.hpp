@@ -80,16 +80,6 @@ struct Sweep2Tile {
 // other counters at their maxima).
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
-// Fix the point in the program where a node's 19 values are complete:
-// nothing that computes them moves below.
-template <class V>
-__device__ __forceinline__ void complete(V (&v)[19]) {
-  asm volatile(""
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
-                 "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15]),
-                 "+v"(v[16]), "+v"(v[17]), "+v"(v[18]));
-}
-
 // The two steps of one workgroup's box: tile (tx, ty) of 64 x BYI nodes and
 // z range tz of a.zc planes, with the population ring `ring` in LDS
 // (kRingPlanes * Sweep2Tile<F, BYI>::kPlane elements).  Every thread of the
