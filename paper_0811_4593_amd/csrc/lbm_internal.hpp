@@ -33,9 +33,10 @@ inline size_t population_pitch(size_t nodes) { return (nodes + 63) / 64 * 64; }
 struct PopLayout {
   size_t pop_stride, row_stride;
   unsigned nx;
+  // (n < 2^31: a 32-bit division, a quarter of the 64-bit one's instructions)
   __host__ __device__ size_t index(int k, size_t n) const {
-    const size_t r = n / nx;
-    return size_t(k) * pop_stride + r * row_stride + (n - r * nx);
+    const unsigned m = unsigned(n), r = m / nx;
+    return size_t(k) * pop_stride + r * row_stride + (m - r * nx);
   }
 };
 inline PopLayout population_major(size_t nodes, int nx) { return {population_pitch(nodes), size_t(nx), unsigned(nx)}; }
