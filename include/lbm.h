@@ -541,7 +541,10 @@ lbm_status lbm_batch_get_shape(const lbm_batch *B, int *block_x, int *tile_nodes
 /* Steps per pass over HBM for the batch's chunks (Sec. II's update, two steps
  * at a time as lbm_set_steps_per_pass does for one lattice):
  *   1 (the default)  one step per launch, except that until this call a chunk
- *                    of one job is grouped as lbm_step groups its steps;
+ *                    of one job is grouped as lbm_step groups its steps, and
+ *                    FP32 and FP64 jobs for which passes are estimated to be
+ *                    faster make them in shared chunks too (those jobs are
+ *                    stored row-major with padded rows);
  *   2                every chunk by passes of two steps: one launch per
  *                    storage form over the 64 x 13 (FP64: 64 x 7) tiles and
  *                    z ranges of z_planes planes (0: 32) of all its jobs, or
@@ -549,13 +552,11 @@ lbm_status lbm_batch_get_shape(const lbm_batch *B, int *block_x, int *tile_nodes
  *                    job; every job is then stored row-major with padded
  *                    rows.
  * Single steps close a chunk whose step count needs them (chunk_steps 2 mod
- * 4: two).  Results are the same bits in either mode.  Two steps per pass
- * pay for batches of large FP32 and FP64 lattices (eight 256^3 cubes: FP32
- * 37.1 -> 40.4 GLUPS, FP64 17.8 -> 23.8), not for small or narrow ones: on
- * 64 uneven ducts of 32-256 x 16-128 x 16-128 nodes they ran 1.3x slower
- * than one step per launch (a quarter of the tiles' lanes fall outside such
- * lattices), and a chunk of one cube of up to 320^3 nodes has too few tiles
- * to fill the chip (FP32 no faster, FP16 1.6x slower).
+ * 4: two).  Results are the same bits in either mode.  Two steps per pass pay
+ * for FP64 jobs of most shapes (64 uneven ducts of 32-256 x 16-128 x 16-128
+ * nodes: 17.3 -> 25.9 GLUPS with z ranges of 16) and for FP32 jobs that fill
+ * the tiles (the same ducts: 37.1 -> 41.6), not for the 16-bit forms (61.3
+ * -> 54.0) nor for batches too small to give every compute unit a box.
  * Errors: LBM_ERR_ARG (steps not 1 or 2, z_planes outside [0, 4096]),
  * LBM_ERR_STATE (a chunk in flight; 2 while a population-major job is queued
  * or resident -- set the mode before submitting). */

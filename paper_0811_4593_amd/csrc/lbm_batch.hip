@@ -579,6 +579,7 @@ struct Job {
   int waited = 0;   // chunks spent at the head of the queue without fitting
   int skipped = 0;  // consecutive scheduling rounds resident, idle and not stepped
   int layout = LBM_LAYOUT_POPULATION_MAJOR;  // chosen at submission
+  bool passes = false;  // takes passes in a shared chunk although one step per pass is set (passes_pay)
   lbm::SweepConfig cfg{};                    // single-lattice sweep of the job (set at admission)
   HostBlock result;  // moments at retirement: rho [N], then u [3][N], in double
 };
@@ -613,7 +614,7 @@ struct Lane {
   std::vector<int> slots;  // slots the chunk in flight steps
   lbm::BatchLat *d_lats = nullptr;
   unsigned *d_delta = nullptr;
-  int *d_ntiles = nullptr;  // tile counts per storage form, then box counts
+  int *d_ntiles = nullptr;  // per storage form: tile counts, box counts, tiles of the jobs without boxes
   lbm::BatchTile *d_tiles[kNumStorage] = {nullptr, nullptr, nullptr, nullptr};
   size_t tile_cap[kNumStorage] = {0, 0, 0, 0};
   lbm::BatchBox *d_boxes[kNumStorage] = {nullptr, nullptr, nullptr, nullptr};  // the two-step pass's boxes
@@ -621,6 +622,7 @@ struct Lane {
   HostBlock h_lats, h_delta, h_ntiles, h_tiles[kNumStorage], h_boxes[kNumStorage];
   int ntiles[kNumStorage] = {0, 0, 0, 0};
   int nboxes[kNumStorage] = {0, 0, 0, 0};
+  int nplain[kNumStorage] = {0, 0, 0, 0};  // tiles of the jobs without boxes: the first of the tile list
   // per-wave maxima of the convergence measure taken by a chunk's last step:
   // for a graph chunk 4 per tile-table entry of each storage form (form s
   // from part_off[s]), for a chunk of one job its single sweep's
@@ -630,8 +632,9 @@ struct Lane {
   // job has other extents, so the tables follow the job ids, not the slots.
   std::vector<std::pair<int, int>> table_jobs;
   int table_tile_nodes = 0, table_pass = 0, table_zc = 0;
-  // captured chunks by (storage forms present, chunk steps, block_x, grid,
-  // steps per pass, z planes, box order)
+  // captured chunks by (storage forms present, with tiles, boxes and tiles
+  // without boxes, chunk steps, block_x, grid, steps per pass, z planes, box
+  // order)
   std::map<std::tuple<unsigned, int, int, int, int, int, int>, hipGraphExec_t> graphs;
 };
 
@@ -705,13 +708,13 @@ lbm_status init_lane(lbm_batch *B, Lane &ln, hipStream_t given) {
   const size_t mj = size_t(B->max_jobs);
   bool ok = hipMalloc(&ln.d_lats, sizeof(lbm::BatchLat) * mj) == hipSuccess &&
             hipMalloc(&ln.d_delta, sizeof(unsigned) * mj) == hipSuccess &&
-            hipMalloc(&ln.d_ntiles, sizeof(int) * 2 * kNumStorage) == hipSuccess;
+            hipMalloc(&ln.d_ntiles, sizeof(int) * 3 * kNumStorage) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
     return bfail(LBM_ERR_OOM, "device tables of a lane could not be allocated");
   }
   if (!ln.h_lats.allocate(sizeof(lbm::BatchLat) * mj, true) || !ln.h_delta.allocate(sizeof(unsigned) * mj, true) ||
-      !ln.h_ntiles.allocate(sizeof(int) * 2 * kNumStorage, true))
+      !ln.h_ntiles.allocate(sizeof(int) * 3 * kNumStorage, true))
     return bfail(LBM_ERR_OOM, "page-locked staging of a lane could not be allocated");
   std::memset(ln.h_lats.as<void>(), 0, ln.h_lats.bytes());
   return LBM_OK;
@@ -759,10 +762,44 @@ lbm_status ensure_partials(Lane &ln, size_t n) {
   return LBM_OK;
 }
 
+// Planes per workgroup of the passes that a shared chunk makes without being
+// asked for.
+constexpr int kAutoPlanes = 16;
+
+int pass_planes(const lbm_batch *B) { return B->pass_steps == 2 ? B->pass_zc : kAutoPlanes; }
+
+// Tiles across and up, and z ranges of zc planes, of a job's boxes.
+struct Boxes {
+  unsigned x, y, z;
+};
+Boxes boxes_of(const lbm_job &j, int zc) {
+  const unsigned by = unsigned(lbm::sweep2_rows(j.storage, 0));
+  return {(unsigned(j.nx) + 63u) / 64u, (unsigned(j.ny) + by - 1u) / by, (unsigned(j.nz) + unsigned(zc) - 1u) / unsigned(zc)};
+}
+
+// Whether passes of two steps are estimated to take a job less of the device
+// than two steps of the batch sweep, by 5% or more.  Every plane of a box
+// (and two more per z range) takes a compute unit 7.2 us in FP32, 6.4 in
+// FP64, however much of the tile the lattice fills; the batch sweep moves
+// 5.4-5.6 TB/s.  On 64 uneven ducts FP32 1.32 -> 1.18 ms per step with passes
+// for all of them, FP64 2.84 -> 1.89; FP16 0.80 -> 0.91, so not there.
+bool passes_pay(const lbm_job &j, int num_cu) {
+  if (j.storage != LBM_STORE_F64 && j.storage != LBM_STORE_F32) return false;
+  const bool f64 = j.storage == LBM_STORE_F64;
+  const Boxes b = boxes_of(j, kAutoPlanes);
+  const double rounds = double(b.x) * b.y * (double(j.nz) + 2.0 * b.z);
+  const double pass_us = rounds * (f64 ? 6.4 : 7.2) / num_cu;
+  const double sweep_us = 2.0 * 38.0 * (f64 ? 8 : 4) * double(j.nx) * j.ny * j.nz / (f64 ? 5.4e6 : 5.6e6);
+  return pass_us < 0.95 * sweep_us;
+}
+
 unsigned present_mask(const Lane &ln) {
   unsigned m = 0;
-  for (int s = 0; s < kNumStorage; ++s)
+  for (int s = 0; s < kNumStorage; ++s) {
     if (ln.ntiles[s] > 0) m |= 1u << s;
+    if (ln.nboxes[s] > 0) m |= 1u << (kNumStorage + s);
+    if (ln.nplain[s] > 0) m |= 1u << (2 * kNumStorage + s);
+  }
   return m;
 }
 
@@ -774,27 +811,43 @@ lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) 
   std::vector<std::pair<int, int>> jobs;
   for (int slot : slots) jobs.push_back({slot, B->slot_job[slot]});
   const bool pass2 = B->pass_steps == 2;
-  if (jobs != ln.table_jobs || ln.table_tile_nodes != B->shape.tile_nodes || ln.table_pass != B->pass_steps ||
+  if (jobs != ln.table_jobs || ln.table_tile_nodes != B->shape.tile_nodes || ln.table_pass != (B->pass_auto ? 0 : B->pass_steps) ||
       ln.table_zc != B->pass_zc) {
     std::vector<lbm::BatchTile> tiles[kNumStorage];
     std::vector<lbm::BatchBox> boxes[kNumStorage];
     const unsigned tn = unsigned(B->shape.tile_nodes);
+    const int zc = pass_planes(B);
+    // Jobs that take passes: all with two steps per pass; otherwise those of
+    // a storage form for which they pay, if their boxes give every compute
+    // unit one (a launch of fewer takes as long).
+    size_t candidates[kNumStorage] = {0, 0, 0, 0};
     for (int slot : slots) {
       const Job &J = B->jobs.at(B->slot_job[slot]);
-      const int st = J.spec.storage;
-      const unsigned S = unsigned(size_t(B->lat[slot].slot_row) * J.spec.ny * J.spec.nz);  // slots of the job
-      for (unsigned n0 = 0; n0 < S; n0 += tn) tiles[st].push_back({slot, n0, std::min(S, n0 + tn)});
-      if (!pass2) continue;
-      if (J.layout != LBM_LAYOUT_ROW_MAJOR)
-        return bfail(LBM_ERR_STATE, "job %d is not row-major: two steps per pass need every job row-major",
-                     B->slot_job[slot]);
-      // boxes z range by z range, row of tiles by row of tiles
-      const unsigned by = unsigned(lbm::sweep2_rows(st, 0)), zc = unsigned(B->pass_zc);
-      const unsigned tx = (unsigned(J.spec.nx) + 63u) / 64u, ty = (unsigned(J.spec.ny) + by - 1u) / by;
-      const unsigned tz = (unsigned(J.spec.nz) + zc - 1u) / zc;
-      for (unsigned z = 0; z < tz; ++z)
-        for (unsigned y = 0; y < ty; ++y)
-          for (unsigned x = 0; x < tx; ++x) boxes[st].push_back({slot, x, y, z});
+      const Boxes b = boxes_of(J.spec, zc);
+      if (J.passes && B->pass_auto) candidates[J.spec.storage] += size_t(b.x) * b.y * b.z;
+    }
+    auto takes_passes = [&](const Job &J) {
+      return pass2 || (J.passes && B->pass_auto && candidates[J.spec.storage] >= size_t(B->num_cu));
+    };
+    for (int with_boxes = 0; with_boxes < 2; ++with_boxes) {
+      for (int slot : slots) {
+        const Job &J = B->jobs.at(B->slot_job[slot]);
+        if (int(takes_passes(J)) != with_boxes) continue;
+        const int st = J.spec.storage;
+        const unsigned S = unsigned(size_t(B->lat[slot].slot_row) * J.spec.ny * J.spec.nz);  // slots of the job
+        for (unsigned n0 = 0; n0 < S; n0 += tn) tiles[st].push_back({slot, n0, std::min(S, n0 + tn)});
+        if (!with_boxes) continue;
+        if (J.layout != LBM_LAYOUT_ROW_MAJOR)
+          return bfail(LBM_ERR_STATE, "job %d is not row-major: two steps per pass need every job row-major",
+                       B->slot_job[slot]);
+        // boxes z range by z range, row of tiles by row of tiles
+        const Boxes b = boxes_of(J.spec, zc);
+        for (unsigned z = 0; z < b.z; ++z)
+          for (unsigned y = 0; y < b.y; ++y)
+            for (unsigned x = 0; x < b.x; ++x) boxes[st].push_back({slot, x, y, z});
+      }
+      if (!with_boxes)
+        for (int st = 0; st < kNumStorage; ++st) ln.nplain[st] = int(tiles[st].size());
     }
     int *counts = ln.h_ntiles.as<int>();
     for (int s = 0; s < kNumStorage; ++s) {
@@ -817,8 +870,9 @@ lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) 
       }
       counts[s] = ln.ntiles[s];
       counts[kNumStorage + s] = ln.nboxes[s];
+      counts[2 * kNumStorage + s] = ln.nplain[s];
     }
-    LBM_BHIP(hipMemcpyAsync(ln.d_ntiles, counts, sizeof(int) * 2 * kNumStorage, hipMemcpyHostToDevice, ln.stream),
+    LBM_BHIP(hipMemcpyAsync(ln.d_ntiles, counts, sizeof(int) * 3 * kNumStorage, hipMemcpyHostToDevice, ln.stream),
              "upload tile and box counts");
     size_t np = 0;
     for (int s = 0; s < kNumStorage; ++s) {
@@ -829,7 +883,7 @@ lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) 
     if (st != LBM_OK) return st;
     ln.table_jobs = jobs;
     ln.table_tile_nodes = B->shape.tile_nodes;
-    ln.table_pass = B->pass_steps;
+    ln.table_pass = B->pass_auto ? 0 : B->pass_steps;
     ln.table_zc = B->pass_zc;
   }
   lbm::BatchLat *h = ln.h_lats.as<lbm::BatchLat>();
@@ -868,24 +922,29 @@ int passes_in(int nsteps) {
 // workgroup per entry of the box table in the same way.  measure: the
 // sequence ends a chunk and its last step (a single step with one workgroup
 // per tile) also takes the convergence measure into the lane's partials.
+//
+// Without two steps per pass set, the jobs with boxes make passes and then at
+// least one single step, so that the last step can take the measure; the
+// other jobs (the first of the tile list) make single steps throughout.
 lbm_status launch_steps(lbm_batch *B, Lane &ln, int nsteps, int first, bool measure) {
-  const int P = B->pass_steps == 2 ? passes_in(nsteps) : 0;
-  for (int i = 0; i < P; ++i)
-    for (int s = 0; s < kNumStorage; ++s)
-      if (ln.nboxes[s] > 0)
-        LBM_BHIP(lbm::launch_batch_pass(s, ln.d_lats, ln.d_boxes[s], ln.d_ntiles + kNumStorage + s, first + 2 * i,
-                                        i & 1, B->pass_zc, B->pass_remap, int(ln.box_cap[s]), ln.stream),
-                 "batch pass launch");
-  for (int j = 2 * P; j < nsteps; ++j) {
-    const int parity = (j - P) & 1;  // buffer flips so far: P passes and j - 2P single steps
-    for (int s = 0; s < kNumStorage; ++s)
-      if (ln.ntiles[s] > 0) {
-        const int grid = B->shape.grid > 0 ? B->shape.grid : int(ln.tile_cap[s]);
-        LBM_BHIP(lbm::launch_batch_sweep(s, B->shape.block_x, ln.d_lats, ln.d_tiles[s], ln.d_ntiles + s, first + j,
-                                         parity, measure && j == nsteps - 1 ? ln.d_part + ln.part_off[s] : nullptr,
-                                         grid, B->shape.grid == 0, ln.stream),
-                 "batch sweep launch");
-      }
+  for (int s = 0; s < kNumStorage; ++s) {
+    if (ln.ntiles[s] == 0) continue;
+    const int grid = B->shape.grid > 0 ? B->shape.grid : int(ln.tile_cap[s]);
+    const int P = ln.nboxes[s] == 0 ? 0 : (B->pass_steps == 2 ? passes_in(nsteps) : ((nsteps - 1) / 2) & ~1);
+    for (int i = 0; i < P; ++i)
+      LBM_BHIP(lbm::launch_batch_pass(s, ln.d_lats, ln.d_boxes[s], ln.d_ntiles + kNumStorage + s, first + 2 * i, i & 1,
+                                      pass_planes(B), B->pass_remap, int(ln.box_cap[s]), ln.stream),
+               "batch pass launch");
+    // (the jobs with boxes: P, an even number of passes, then single steps;
+    // the others' buffers flip once a step)
+    for (int j = ln.nplain[s] > 0 ? 0 : 2 * P; j < nsteps; ++j) {
+      const bool all = j >= 2 * P;
+      LBM_BHIP(lbm::launch_batch_sweep(s, B->shape.block_x, ln.d_lats, ln.d_tiles[s],
+                                       ln.d_ntiles + (all ? 0 : 2 * kNumStorage) + s, first + j, j & 1,
+                                       measure && j == nsteps - 1 ? ln.d_part + ln.part_off[s] : nullptr, grid,
+                                       B->shape.grid == 0, ln.stream),
+               "batch sweep launch");
+    }
   }
   return LBM_OK;
 }
@@ -1507,8 +1566,10 @@ lbm_status lbm_batch_submit(lbm_batch *B, const lbm_job *job, int *job_id) {
   // rows of whole 128-byte lines.
   const bool alone = B->policy == LBM_BATCH_LARGE_IN_ORDER ||
                      (B->policy == LBM_BATCH_SHORTEST_FIRST && double(J.nodes) >= double(B->fill_nodes));
-  J.layout = (alone || B->pass_steps == 2) ? LBM_LAYOUT_ROW_MAJOR
-                                           : batch_layout_kind(j.nx, lbm_element_bytes(j.storage));
+  // Likewise for a job that takes passes without being asked for.
+  J.passes = B->pass_steps == 1 && B->pass_auto && passes_pay(j, B->num_cu);
+  J.layout = (alone || B->pass_steps == 2 || J.passes) ? LBM_LAYOUT_ROW_MAJOR
+                                                       : batch_layout_kind(j.nx, lbm_element_bytes(j.storage));
   J.bytes = job_bytes(j, J.layout);
   if (J.bytes > B->pool.capacity())
     return bfail(LBM_ERR_OOM, "job needs %zu bytes, more than the whole budget (%zu)", J.bytes, B->pool.capacity());

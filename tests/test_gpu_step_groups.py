@@ -118,3 +118,34 @@ def test_single_jobs_of_a_batch(storage, chunk):
             np.testing.assert_array_equal(u, v)
     finally:
         lbm.lbm_batch_destroy(b)
+
+
+@pytest.mark.parametrize("chunk", [4, 10, 50])
+@pytest.mark.parametrize("shape", [(256, 256, 0), (128, 1024, 64)], ids=["a-workgroup-per-tile", "persistent"])
+def test_shared_chunks(chunk, shape):
+    """A lockstep batch whose larger FP32 and FP64 jobs make passes beside
+    jobs that do not (narrow, 16-bit), the convergence measure included."""
+    items = [(workloads.duct(250, 120, 100, (0.03, 0.01, 0.0), 0.9), "f32"),
+             (workloads.duct(33, 91, 20, (0.02, 0.01, 0.01), 0.8), "f32"),
+             (workloads.duct(200, 100, 60, (0.04, 0.01, 0.01), 0.8), "f64"),
+             (workloads.duct(130, 70, 64, (0.02, -0.01, 0.01), 1.1), "f64"),
+             (workloads.duct(64, 20, 20, (0.03, 0.0, 0.01), 0.9), "f16sr")]
+    steps = 2 * chunk
+    got = []
+    for one_step in (False, True):
+        b = lbm.lbm_batch_create(2 << 30, chunk, 8)
+        try:
+            if one_step:
+                lbm.lbm_batch_set_steps_per_pass(b, 1, 0)
+            lbm.lbm_batch_set_shape(b, *shape)
+            ids = [lbm.lbm_batch_submit(b, serving.job_for(s, st, 0.0, steps)) for s, st in items]
+            while lbm.lbm_batch_run_chunk(b) != (0, 0):
+                pass
+            got.append([(lbm.lbm_batch_poll(b, i).delta, *lbm.lbm_batch_result(b, i, s.nodes))
+                        for i, (s, _) in zip(ids, items)])
+        finally:
+            lbm.lbm_batch_destroy(b)
+    for (s, st), x, y in zip(items, *got):
+        assert x[0] == y[0], (s.name, st)
+        np.testing.assert_array_equal(x[1], y[1], err_msg=s.name)
+        np.testing.assert_array_equal(x[2], y[2], err_msg=s.name)
