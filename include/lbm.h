@@ -345,9 +345,8 @@ lbm_status lbm_get_launch(const lbm_lattice *L, int *block_x, int *nodes_per_thr
  * planes per workgroup; the first step on the two planes beyond a range is
  * done by both neighbouring ranges.  tile_rows picks the tile height: 0,
  * the form's default; 5, five-row tiles (two workgroups per compute unit);
- * 12, twelve-row tiles (15 waves, three of step 2's 12 on each SIMD;
- * measured faster than 13 rows on 512 x 256 x 256 FP32, slower on
- * 1024 x 512 x 512); FP64 tiles have seven rows either way.  Every variant
+ * 12, twelve-row tiles (15 waves, three of step 2's 12 on each SIMD; within
+ * 4% of 13 rows either way); FP64 tiles have seven rows either way.  Every variant
  * gives the same bits.  steps_per_pass = 1: one single sweep per step (the
  * default); small lattices (up to about 65000 nodes, without those options)
  * make two or three steps per launch, and until this call, lbm_set_launch or

@@ -72,6 +72,9 @@ static hipError_t launch_sweep2_t(const SweepConfig &c, int zc, const void *src,
   return hipGetLastError();
 }
 
+// Row-major, with planes below 4 GiB: the pass addresses a plane by 32-bit
+// offsets within one buffer descriptor.  Larger planes (28 million FP64 or 56
+// million FP32 nodes each) take the single sweep.
 bool sweep2_takes(const PopLayout &lay, int ny, int storage) {
   const size_t esize = storage == kStoreF64 ? 8 : (storage == kStoreF32 ? 4 : 2);
   return lay.row_stride == 19 * lay.pop_stride && lay.row_stride * esize * size_t(ny) < (size_t(1) << 32);

@@ -97,9 +97,15 @@ __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70
 // that loads, waits, computes and stores in turn leaves memory idle through
 // the arithmetic and the other way round: without any arithmetic it still
 // took 8.9 ms on the 1024 x 512 x 512 FP32 duct, with it 11.1 ms, this way
-// 8.5 ms (9.6 TB/s at the algorithmic 152 B per update).  512 x 256 x 256
-// FP64: 2.87 ms, 2.19 ms with the loads ahead and 7 rows (5 rows 2.38 ms, 6
-// rows 2.17-2.23 ms).
+// 8.5-9.0 ms by the allocation (9.1-9.6 TB/s at the algorithmic 152 B per
+// update; without arithmetic 8.1 ms).  512 x 256 x 256 FP64: 2.87 ms, 2.19 ms
+// with the loads ahead and 7 rows (5 rows 2.38 ms, 6 rows 2.17-2.23 ms),
+// 2.0-2.1 ms with one descriptor per plane and the shorter boundary rules.
+//
+// Every wave keeps to one row, so that its loads and stores are whole cache
+// lines of it.  Lanes dealt to tiles of any width instead (rows of 200 nodes
+// leave 22% of these idle) took 252 us per step against 188 on 300 x 150 x
+// 200 FP32, 59 against 55 on 200 x 100 x 100: lines written in parts.
 template <class F, int BYI>
 __device__ __forceinline__ void sweep2_box(global_ptr<const typename F::S> src, global_ptr<typename F::S> dst,
                                            const Sweep2Args<typename Codec<typename F::S>::T> &a, unsigned tx,
