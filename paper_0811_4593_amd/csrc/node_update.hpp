@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
+#include <type_traits>
 
 #include "d3q19.hpp"
 
@@ -511,7 +512,7 @@ __device__ __forceinline__ void update_node(const Access &mem, const NodeGeom &g
       }
       boundary_rule<T>(f, m, p, p.p_mask, vx, vy, vz, r0);
     }
-    bgk_collide<T>(f, p.omega, p.tau_f);
+    bgk_collide<T, EXT && std::is_same<F, FormF16>::value>(f, p.omega, p.tau_f);
     // Random words of the stochastic rounding: a hash of (node, step), then
     // a golden-ratio Weyl sequence over the populations (each word uniform;
     // only its top 13 bits are used).
