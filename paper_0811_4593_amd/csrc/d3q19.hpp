@@ -472,9 +472,9 @@ __device__ __forceinline__ void general_wall_rule(T (&d)[19], unsigned U) {
 // c_k . u of a diagonal link is one component's momentum times 1 / rho fused
 // with the other component's velocity; whether the first component is the
 // fused one.  x_first: that of every link with an x component is.  The
-// extended sweep of FP16 with round-to-nearest has always summed them so; it
-// moves 4 in 10^5 values of the six links that differ by half a unit of the
-// stored half, so a run that is continued or repeated needs it kept.
+// extended sweep of FP16 with round-to-nearest has always summed them so; the
+// other way 12 in 10^5 values of the six links that differ move by half a unit
+// of the stored half, so a run that is continued or repeated needs it kept.
 __host__ __device__ constexpr bool fuses_first(int k, bool x_first) {
   return cx(k) ? (x_first || (cx(k) < 0 && cy(k) + cz(k) < 0)) : !(cy(k) < 0 && cz(k) > 0);
 }

@@ -1413,13 +1413,18 @@ int count_active(const lbm_batch *B) {
   return n;
 }
 
+// Key of the shared autotune results: the forms present (with tiles, boxes and
+// tiles without boxes), log2 of the resident nodes and the steps per pass, each
+// in bits of its own.  (Without boxes one step per pass as the default and as
+// asked for are the same work and share a result.)
 long long tune_key(const lbm_batch *B, const Lane &ln) {
   size_t nodes = 0;
   for (int id : B->slot_job)
     if (id >= 0) nodes += B->jobs.at(id).nodes;
   int lg = 0;
   while ((size_t(1) << lg) < nodes) ++lg;
-  return (long long)present_mask(ln) | ((long long)lg << 4) | ((long long)B->pass_steps << 12);
+  constexpr int kMaskBits = 3 * kNumStorage;
+  return (long long)present_mask(ln) | ((long long)lg << kMaskBits) | ((long long)B->pass_steps << (kMaskBits + 8));
 }
 
 }  // namespace
