@@ -12,6 +12,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <deque>
@@ -580,6 +581,7 @@ struct Job {
   int skipped = 0;  // consecutive scheduling rounds resident, idle and not stepped
   int layout = LBM_LAYOUT_POPULATION_MAJOR;  // chosen at submission
   bool passes = false;  // takes passes in a shared chunk although one step per pass is set (passes_pay)
+  bool for_passes = false;  // row-major for that reason alone
   lbm::SweepConfig cfg{};                    // single-lattice sweep of the job (set at admission)
   HostBlock result;  // moments at retirement: rho [N], then u [3][N], in double
 };
@@ -791,6 +793,19 @@ bool passes_pay(const lbm_job &j, int num_cu) {
   const double pass_us = rounds * (f64 ? 6.4 : 7.2) / num_cu;
   const double sweep_us = 2.0 * 38.0 * (f64 ? 8 : 4) * double(j.nx) * j.ny * j.nz / (f64 ? 5.4e6 : 5.6e6);
   return pass_us < 0.95 * sweep_us;
+}
+
+// Bytes of a job that has not started without padding it for passes (its own
+// where it is not padded for them), and that layout for it.
+size_t unpadded_bytes(const Job &J) {
+  if (!J.for_passes) return J.bytes;
+  return std::min(J.bytes, job_bytes(J.spec, batch_layout_kind(J.spec.nx, lbm_element_bytes(J.spec.storage))));
+}
+void drop_padding(Job &J) {
+  if (unpadded_bytes(J) == J.bytes) return;
+  J.bytes = unpadded_bytes(J);
+  J.layout = batch_layout_kind(J.spec.nx, lbm_element_bytes(J.spec.storage));
+  J.passes = J.for_passes = false;
 }
 
 unsigned present_mask(const Lane &ln) {
@@ -1081,8 +1096,16 @@ lbm_status retire(lbm_batch *B, int id, Lane &ln) {
 // Admit queued jobs in arrival order while memory and slots allow.  A job may
 // pass the head of the queue only while the head has waited fewer than four
 // chunks, so large jobs are not starved by a stream of small ones.
+//
+// The padded rows of jobs that make passes without being asked to are no
+// reason to let a job wait: where all queued jobs fit at once without that
+// padding, it takes only what they leave; and a job that does not fit with it
+// goes without.
 lbm_status admit(lbm_batch *B) {
   bool head_blocked = false;
+  size_t need = 0, slack = B->pool.capacity() - B->pool.used();
+  for (int id : B->queue) need += align_up(unpadded_bytes(B->jobs.at(id)));
+  slack = need <= slack ? slack - need : SIZE_MAX;
   for (auto it = B->queue.begin(); it != B->queue.end();) {
     Job &J = B->jobs.at(*it);
     int slot = -1;
@@ -1092,7 +1115,15 @@ lbm_status admit(lbm_batch *B) {
         break;
       }
     size_t off = 0;
-    if (slot < 0 || !B->pool.alloc(J.bytes, &off)) {
+    const size_t extra = B->pass_steps == 1 ? align_up(J.bytes) - align_up(unpadded_bytes(J)) : 0;
+    bool fits = slot >= 0 && extra <= slack && B->pool.alloc(J.bytes, &off);
+    if (fits) {
+      if (slack != SIZE_MAX) slack -= extra;
+    } else if (slot >= 0 && extra > 0 && B->pool.alloc(unpadded_bytes(J), &off)) {
+      drop_padding(J);
+      fits = true;
+    }
+    if (!fits) {
       if (it == B->queue.begin()) {
         ++J.waited;
         head_blocked = J.waited >= 4;
@@ -1571,11 +1602,14 @@ lbm_status lbm_batch_submit(lbm_batch *B, const lbm_job *job, int *job_id) {
   // rows of whole 128-byte lines.
   const bool alone = B->policy == LBM_BATCH_LARGE_IN_ORDER ||
                      (B->policy == LBM_BATCH_SHORTEST_FIRST && double(J.nodes) >= double(B->fill_nodes));
-  // Likewise for a job that takes passes without being asked for.
+  // Likewise for a job that takes passes without being asked for, as long as
+  // its padded rows fit the budget.
   J.passes = B->pass_steps == 1 && B->pass_auto && passes_pay(j, B->num_cu);
+  J.for_passes = J.passes && !alone;
   J.layout = (alone || B->pass_steps == 2 || J.passes) ? LBM_LAYOUT_ROW_MAJOR
                                                        : batch_layout_kind(j.nx, lbm_element_bytes(j.storage));
   J.bytes = job_bytes(j, J.layout);
+  if (J.bytes > B->pool.capacity()) drop_padding(J);
   if (J.bytes > B->pool.capacity())
     return bfail(LBM_ERR_OOM, "job needs %zu bytes, more than the whole budget (%zu)", J.bytes, B->pool.capacity());
   const int id = B->next_id++;

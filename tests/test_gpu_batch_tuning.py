@@ -30,3 +30,28 @@ def test_sizes_of_one_mix_are_tuned_separately():
     assert _trial_steps(256) > 0
     assert _trial_steps(512) > 0
     assert _trial_steps(256) == 0 and _trial_steps(512) == 0
+
+
+def _flat_bytes(s):
+    """Memory of an FP64 job with its populations one after another, without padded rows."""
+    up = lambda n, m: (n + m - 1) // m * m  # noqa: E731
+    return 2 * up(19 * up(s.nodes, 64) * 8, 256) + up(12 * s.nodes, 256)
+
+
+def test_a_job_fits_the_budget_without_the_padding_of_passes():
+    """Rows of 40 FP64 nodes take 48 with padding: a budget for the unpadded job
+    takes it, and one job and a half at a time do not keep the second waiting."""
+    s = workloads.duct(40, 70, 64, (0.03, 0.01, 0.0), 0.9)
+    fields = []
+    for budget, count in ((4 * _flat_bytes(s), 2), (_flat_bytes(s) + 4096, 1), (int(2.15 * _flat_bytes(s)), 2)):
+        b = lbm.lbm_batch_create(budget, 20, 4)
+        try:
+            ids = [lbm.lbm_batch_submit(b, serving.job_for(s, "f64", 0.0, 40)) for _ in range(count)]
+            assert lbm.lbm_batch_run_chunk(b) == (count, 0)
+            while lbm.lbm_batch_run_chunk(b) != (0, 0):
+                pass
+            fields += [lbm.lbm_batch_result(b, i, s.nodes) for i in ids]
+        finally:
+            lbm.lbm_batch_destroy(b)
+    for rho, u in fields[1:]:
+        assert (rho == fields[0][0]).all() and (u == fields[0][1]).all()
