@@ -768,6 +768,10 @@ lbm_status ensure_partials(Lane &ln, size_t n) {
 // asked for.
 constexpr int kAutoPlanes = 16;
 
+// Passes of a shared chunk of nsteps (even) steps then: an even number, which
+// leaves the chunk at least one single step for the measure.
+int auto_passes_in(int nsteps) { return ((nsteps - 1) / 2) & ~1; }
+
 int pass_planes(const lbm_batch *B) { return B->pass_steps == 2 ? B->pass_zc : kAutoPlanes; }
 
 // Tiles across and up, and z ranges of zc planes, of a job's boxes.
@@ -945,7 +949,7 @@ lbm_status launch_steps(lbm_batch *B, Lane &ln, int nsteps, int first, bool meas
   for (int s = 0; s < kNumStorage; ++s) {
     if (ln.ntiles[s] == 0) continue;
     const int grid = B->shape.grid > 0 ? B->shape.grid : int(ln.tile_cap[s]);
-    const int P = ln.nboxes[s] == 0 ? 0 : (B->pass_steps == 2 ? passes_in(nsteps) : ((nsteps - 1) / 2) & ~1);
+    const int P = ln.nboxes[s] == 0 ? 0 : (B->pass_steps == 2 ? passes_in(nsteps) : auto_passes_in(nsteps));
     for (int i = 0; i < P; ++i)
       LBM_BHIP(lbm::launch_batch_pass(s, ln.d_lats, ln.d_boxes[s], ln.d_ntiles + kNumStorage + s, first + 2 * i, i & 1,
                                       pass_planes(B), B->pass_remap, int(ln.box_cap[s]), ln.stream),
@@ -1604,7 +1608,7 @@ lbm_status lbm_batch_submit(lbm_batch *B, const lbm_job *job, int *job_id) {
                      (B->policy == LBM_BATCH_SHORTEST_FIRST && double(J.nodes) >= double(B->fill_nodes));
   // Likewise for a job that takes passes without being asked for, as long as
   // its padded rows fit the budget.
-  J.passes = B->pass_steps == 1 && B->pass_auto && passes_pay(j, B->num_cu);
+  J.passes = B->pass_steps == 1 && B->pass_auto && auto_passes_in(B->chunk_steps) > 0 && passes_pay(j, B->num_cu);
   J.for_passes = J.passes && !alone;
   J.layout = (alone || B->pass_steps == 2 || J.passes) ? LBM_LAYOUT_ROW_MAJOR
                                                        : batch_layout_kind(j.nx, lbm_element_bytes(j.storage));

@@ -55,3 +55,17 @@ def test_a_job_fits_the_budget_without_the_padding_of_passes():
             lbm.lbm_batch_destroy(b)
     for rho, u in fields[1:]:
         assert (rho == fields[0][0]).all() and (u == fields[0][1]).all()
+
+
+@pytest.mark.parametrize("chunk, padded", [(2, False), (4, False), (6, True), (100, True)])
+def test_padding_only_where_a_chunk_makes_passes(chunk, padded):
+    """A chunk of up to four steps has no room for a pair of passes before its
+    last step, so its jobs keep their unpadded rows."""
+    s = workloads.duct(40, 70, 64, (0.03, 0.01, 0.0), 0.9)
+    b = lbm.lbm_batch_create(1 << 30, chunk, 4)
+    try:
+        lbm.lbm_batch_submit(b, serving.job_for(s, "f64", 0.0, 1000))
+        lbm.lbm_batch_run_chunk(b)
+        assert (lbm.lbm_batch_memory(b)[0] > _flat_bytes(s)) == padded
+    finally:
+        lbm.lbm_batch_destroy(b)
