@@ -16,10 +16,12 @@
 #include <cstdio>
 #include <cstring>
 #include <deque>
+#include <functional>
 #include <map>
 #include <tuple>
 #include <new>
 #include <mutex>
+#include <queue>
 #include <thread>
 #include <vector>
 
@@ -783,20 +785,80 @@ Boxes boxes_of(const lbm_job &j, int zc) {
   return {(unsigned(j.nx) + 63u) / 64u, (unsigned(j.ny) + by - 1u) / by, (unsigned(j.nz) + unsigned(zc) - 1u) / unsigned(zc)};
 }
 
+// Time of a round of the batch's pass (a plane of a box on a compute unit,
+// however much of the tile the lattice fills), rounds of a job's boxes (two
+// more per z range than it has planes), and time of two steps of a job by the
+// batch sweep, which moves 5.4-5.6 TB/s.
+double pass_round_us(int storage) { return storage == LBM_STORE_F64 ? 6.4 : 7.2; }
+double pass_rounds(const lbm_job &j) {
+  const Boxes b = boxes_of(j, kAutoPlanes);
+  return double(b.x) * b.y * (double(j.nz) + 2.0 * b.z);
+}
+double sweep_pair_us(const lbm_job &j) {
+  const bool f64 = j.storage == LBM_STORE_F64;
+  return 2.0 * 38.0 * (f64 ? 8 : 4) * double(j.nx) * j.ny * j.nz / (f64 ? 5.4e6 : 5.6e6);
+}
+
 // Whether passes of two steps are estimated to take a job less of the device
-// than two steps of the batch sweep, by 5% or more.  Every plane of a box
-// (and two more per z range) takes a compute unit 7.2 us in FP32, 6.4 in
-// FP64, however much of the tile the lattice fills; the batch sweep moves
-// 5.4-5.6 TB/s.  On 64 uneven ducts FP32 1.32 -> 1.18 ms per step with passes
-// for all of them, FP64 2.84 -> 1.89; FP16 0.80 -> 0.91, so not there.
+// than two steps of the batch sweep, by 5% or more.  On 64 uneven ducts FP32
+// 1.32 -> 1.18 ms per step with passes for all of them, FP64 2.84 -> 1.89;
+// FP16 0.80 -> 0.91, so not there.
 bool passes_pay(const lbm_job &j, int num_cu) {
   if (j.storage != LBM_STORE_F64 && j.storage != LBM_STORE_F32) return false;
-  const bool f64 = j.storage == LBM_STORE_F64;
-  const Boxes b = boxes_of(j, kAutoPlanes);
-  const double rounds = double(b.x) * b.y * (double(j.nz) + 2.0 * b.z);
-  const double pass_us = rounds * (f64 ? 6.4 : 7.2) / num_cu;
-  const double sweep_us = 2.0 * 38.0 * (f64 ? 8 : 4) * double(j.nx) * j.ny * j.nz / (f64 ? 5.4e6 : 5.6e6);
-  return pass_us < 0.95 * sweep_us;
+  return pass_rounds(j) * pass_round_us(j.storage) / num_cu < 0.95 * sweep_pair_us(j);
+}
+
+// Boxes of the jobs of one storage form that would make passes together, as
+// (boxes, rounds of each) in the order of the box list, and the time of two
+// steps of those jobs by the batch sweep.
+struct PassLoad {
+  std::vector<std::pair<size_t, int>> boxes;
+  double sweep_us = 0.0;
+  void add(const lbm_job &j) {
+    const Boxes b = boxes_of(j, kAutoPlanes);
+    for (unsigned z = 0; z < b.z; ++z)
+      boxes.push_back({size_t(b.x) * b.y, std::min(kAutoPlanes, j.nz - int(z) * kAutoPlanes) + 2});
+    sweep_us += sweep_pair_us(j);
+  }
+};
+
+// Rounds until a launch of these boxes ends on `units` compute units, each
+// taking the next box as it ends one.
+double launch_rounds(const PassLoad &p, size_t units) {
+  size_t n = 0;
+  double rounds = 0.0;
+  for (const auto &b : p.boxes) {
+    n += b.first;
+    rounds += double(b.first) * b.second;
+  }
+  if (n > 64 * units) return rounds / double(units) + kAutoPlanes + 2;  // many waves: the last one hardly counts
+  std::priority_queue<int, std::vector<int>, std::greater<int>> free_at;
+  int last = 0;
+  for (const auto &b : p.boxes)
+    for (size_t i = 0; i < b.first; ++i) {
+      int at = 0;
+      if (free_at.size() == units) {
+        at = free_at.top();
+        free_at.pop();
+      }
+      free_at.push(at + b.second);
+      last = std::max(last, at + b.second);
+    }
+  return double(last);
+}
+
+// Whether these jobs make passes in a chunk of one of `lanes` lanes, which
+// share the device: their boxes give every compute unit one (a launch of
+// fewer takes as long), and passes take less time than sweeps by 5%, the last
+// wave of boxes included, which may be nearly empty.  Single lane, FP32, us
+// per step by sweeps and passes: four 100^3 ducts (448 boxes for 256 units:
+// 36 rounds) 110 / 131, four of 112^3 (504: 36) 174 / 135; the first ten of
+// the 64 uneven ducts 222 / 238, the first sixteen 365 / 358.
+bool chunk_passes_pay(const PassLoad &p, int storage, int num_cu, size_t lanes) {
+  const size_t units = std::max<size_t>(1, size_t(num_cu) / lanes);
+  size_t n = 0;
+  for (const auto &b : p.boxes) n += b.first;
+  return n >= units && launch_rounds(p, units) * pass_round_us(storage) < 0.95 * p.sweep_us * double(lanes);
 }
 
 // Bytes of a job that has not started without padding it for passes (its own
@@ -804,6 +866,24 @@ bool passes_pay(const lbm_job &j, int num_cu) {
 size_t unpadded_bytes(const Job &J) {
   if (!J.for_passes) return J.bytes;
   return std::min(J.bytes, job_bytes(J.spec, batch_layout_kind(J.spec.nx, lbm_element_bytes(J.spec.storage))));
+}
+
+// Whether a queued job padded for passes is worth the padding.  shared: there
+// are more jobs than lanes, and those of its form make passes in their chunks;
+// otherwise every job has a lane to itself, and the job's own kernels have to
+// group its steps (run_solo_chunk).  Without either, padded rows only cost:
+// four 50 x 78 x 80 FP32 ducts, too few boxes for passes, take 40 us per step
+// unpadded and 49 padded; one of 100^3 33 and 37; four of 100^3 on a lane
+// each 116 and 143.
+bool padding_pays(const lbm_batch *B, const Job &J, bool shared, bool passes) {
+  if (shared) return passes;
+  lbm::SweepConfig c{};
+  c.storage = J.spec.storage;
+  c.nx = J.spec.nx;
+  c.ny = J.spec.ny;
+  c.nz = J.spec.nz;
+  c.layout = layout_of(LBM_LAYOUT_ROW_MAJOR, J.nodes, c.nx, lbm_element_bytes(J.spec.storage));
+  return lbm::block_steps(c) > 0 || lbm::sweep2_pays(c, B->num_cu) > 0;
 }
 void drop_padding(Job &J) {
   if (unpadded_bytes(J) == J.bytes) return;
@@ -837,17 +917,15 @@ lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) 
     const unsigned tn = unsigned(B->shape.tile_nodes);
     const int zc = pass_planes(B);
     // Jobs that take passes: all with two steps per pass; otherwise those of
-    // a storage form for which they pay, if their boxes give every compute
-    // unit one (a launch of fewer takes as long).
-    size_t candidates[kNumStorage] = {0, 0, 0, 0};
+    // a storage form for which they pay together.
+    PassLoad load[kNumStorage];
+    bool pays[kNumStorage];
     for (int slot : slots) {
       const Job &J = B->jobs.at(B->slot_job[slot]);
-      const Boxes b = boxes_of(J.spec, zc);
-      if (J.passes && B->pass_auto) candidates[J.spec.storage] += size_t(b.x) * b.y * b.z;
+      if (J.passes && B->pass_auto) load[J.spec.storage].add(J.spec);
     }
-    auto takes_passes = [&](const Job &J) {
-      return pass2 || (J.passes && B->pass_auto && candidates[J.spec.storage] >= size_t(B->num_cu));
-    };
+    for (int st = 0; st < kNumStorage; ++st) pays[st] = chunk_passes_pay(load[st], st, B->num_cu, B->lanes.size());
+    auto takes_passes = [&](const Job &J) { return pass2 || (J.passes && B->pass_auto && pays[J.spec.storage]); };
     for (int with_boxes = 0; with_boxes < 2; ++with_boxes) {
       for (int slot : slots) {
         const Job &J = B->jobs.at(B->slot_job[slot]);
@@ -1106,7 +1184,28 @@ lbm_status retire(lbm_batch *B, int id, Lane &ln) {
 // padding, it takes only what they leave; and a job that does not fit with it
 // goes without.
 lbm_status admit(lbm_batch *B) {
+  if (B->queue.empty()) return LBM_OK;
   bool head_blocked = false;
+  if (B->pass_steps == 1) {
+    std::vector<const Job *> jobs;
+    for (int id : B->slot_job)
+      if (id >= 0) jobs.push_back(&B->jobs.at(id));
+    for (int id : B->queue) jobs.push_back(&B->jobs.at(id));
+    const bool shared = jobs.size() > B->lanes.size();
+    int passes[kNumStorage] = {-1, -1, -1, -1};  // not asked, no, yes
+    for (int id : B->queue) {
+      Job &J = B->jobs.at(id);
+      if (!J.for_passes) continue;
+      int &p = passes[J.spec.storage];
+      if (shared && p < 0) {
+        PassLoad load;
+        for (const Job *o : jobs)
+          if (o->passes && o->spec.storage == J.spec.storage) load.add(o->spec);
+        p = chunk_passes_pay(load, J.spec.storage, B->num_cu, 1);
+      }
+      if (!padding_pays(B, J, shared, p > 0)) drop_padding(J);
+    }
+  }
   size_t need = 0, slack = B->pool.capacity() - B->pool.used();
   for (int id : B->queue) need += align_up(unpadded_bytes(B->jobs.at(id)));
   slack = need <= slack ? slack - need : SIZE_MAX;

@@ -57,15 +57,37 @@ def test_a_job_fits_the_budget_without_the_padding_of_passes():
         assert (rho == fields[0][0]).all() and (u == fields[0][1]).all()
 
 
+def _padded(jobs, chunk, lanes=1):
+    """Which of the queued FP64 ducts (extents) a batch stores with padded rows."""
+    b = lbm.lbm_batch_create(4 << 30, chunk, len(jobs))
+    try:
+        lbm.lbm_batch_set_lanes(b, lanes)
+        specs = [workloads.duct(*d, (0.03, 0.01, 0.0), 0.9) for d in jobs]
+        for s in specs:
+            lbm.lbm_batch_submit(b, serving.job_for(s, "f64", 0.0, 1000))
+        lbm.lbm_batch_run_chunk(b)
+        return lbm.lbm_batch_memory(b)[0] > sum(_flat_bytes(s) for s in specs)
+    finally:
+        lbm.lbm_batch_destroy(b)
+
+
 @pytest.mark.parametrize("chunk, padded", [(2, False), (4, False), (6, True), (100, True)])
 def test_padding_only_where_a_chunk_makes_passes(chunk, padded):
     """A chunk of up to four steps has no room for a pair of passes before its
     last step, so its jobs keep their unpadded rows."""
-    s = workloads.duct(40, 70, 64, (0.03, 0.01, 0.0), 0.9)
-    b = lbm.lbm_batch_create(1 << 30, chunk, 4)
-    try:
-        lbm.lbm_batch_submit(b, serving.job_for(s, "f64", 0.0, 1000))
-        lbm.lbm_batch_run_chunk(b)
-        assert (lbm.lbm_batch_memory(b)[0] > _flat_bytes(s)) == padded
-    finally:
-        lbm.lbm_batch_destroy(b)
+    assert _padded([(40, 70, 64)] * 25, chunk) == padded
+
+
+@pytest.mark.parametrize("lanes", [1, 4])
+@pytest.mark.parametrize("jobs, padded", [
+    ([(40, 70, 64)] * 5, False),     # 200 boxes: less than one per compute unit
+    ([(40, 70, 64)] * 8, False),     # 320 boxes, the second wave nearly empty
+    ([(40, 70, 64)] * 100, True),    # thousands of boxes
+    ([(40, 70, 64)], False),         # alone, steps not grouped
+    ([(100, 100, 100)], True),       # alone, by passes
+    ([(40, 28, 32)], True),          # alone, by blocks of steps
+], ids=["few", "empty-wave", "many", "alone", "alone-passes", "alone-blocks"])
+def test_padding_only_where_steps_are_grouped(jobs, padded, lanes):
+    if len(jobs) == 100:
+        jobs = [(40, 70, 16)] * 300 if lanes == 4 else jobs[:25]  # 3000 and 1000 boxes
+    assert _padded(jobs, 100, lanes) == padded
