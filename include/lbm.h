@@ -566,7 +566,11 @@ lbm_status lbm_batch_get_steps_per_pass(const lbm_batch *B, int *steps_per_pass,
  * for each candidate shape (one workgroup per tile: 256 threads and tiles of
  * 256, 512 or 1024 nodes, 128 threads and 256 nodes; persistent: 256 threads,
  * 1024-node tiles, 16 workgroups per compute unit, and 128 threads, 1024
- * nodes, 8 per compute unit) and keep the fastest; with two steps per pass,
+ * nodes, 8 per compute unit), after two warm-up steps, and keep the fastest.
+ * Jobs that make passes by default make them for all of the trial steps but
+ * the last ones here too (none for trial_steps 2); the shape is chosen by the
+ * time of the single steps, and the passes, timed apart, choose their box
+ * order.  With two steps per pass,
  * z ranges of 16, 32 or 64 planes in two box orders (each XCD a contiguous
  * share of the box list, or dispatch order), timed over trial_steps rounded
  * up to a multiple of 4 (at least 4) after 4 warm-up steps.  The trial steps are

@@ -657,6 +657,7 @@ struct lbm_batch {
   // workgroup, box order pass_remap on the XCDs.
   int pass_steps = 1, pass_zc = 32, pass_remap = 1;
   bool pass_auto = true;  // lbm_batch_set_steps_per_pass has not been called
+  long long pass_launches = 0;  // multi-lattice passes enqueued (those of a captured chunk once)
   std::map<int, Job> jobs;
   std::deque<int> queue;
   std::vector<int> slot_job;           // slot -> job id (-1 free)
@@ -1023,25 +1024,41 @@ int passes_in(int nsteps) {
 // Without two steps per pass set, the jobs with boxes make passes and then at
 // least one single step, so that the last step can take the measure; the
 // other jobs (the first of the tile list) make single steps throughout.
+
+// P passes (even) of the jobs of storage form s that have boxes.
+lbm_status launch_passes(lbm_batch *B, Lane &ln, int s, int P, int first) {
+  for (int i = 0; i < P; ++i)
+    LBM_BHIP(lbm::launch_batch_pass(s, ln.d_lats, ln.d_boxes[s], ln.d_ntiles + kNumStorage + s, first + 2 * i, i & 1,
+                                    pass_planes(B), B->pass_remap, int(ln.box_cap[s]), ln.stream),
+             "batch pass launch");
+  B->pass_launches += P;
+  return LBM_OK;
+}
+
+// The single steps among steps [from, to) of a sequence of nsteps that starts
+// with P passes of the jobs with boxes: those jobs' from step 2 P, the others'
+// all of them (P is even, and the others' buffers flip once a step: the step's
+// index gives the buffers of both).
+lbm_status launch_singles(lbm_batch *B, Lane &ln, int s, int P, int from, int to, int first, bool measure_last) {
+  const int grid = B->shape.grid > 0 ? B->shape.grid : int(ln.tile_cap[s]);
+  for (int j = ln.nplain[s] > 0 ? from : std::max(from, 2 * P); j < to; ++j) {
+    const bool all = j >= 2 * P;
+    LBM_BHIP(lbm::launch_batch_sweep(s, B->shape.block_x, ln.d_lats, ln.d_tiles[s],
+                                     ln.d_ntiles + (all ? 0 : 2 * kNumStorage) + s, first + j, j & 1,
+                                     measure_last && j == to - 1 ? ln.d_part + ln.part_off[s] : nullptr, grid,
+                                     B->shape.grid == 0, ln.stream),
+             "batch sweep launch");
+  }
+  return LBM_OK;
+}
+
 lbm_status launch_steps(lbm_batch *B, Lane &ln, int nsteps, int first, bool measure) {
   for (int s = 0; s < kNumStorage; ++s) {
     if (ln.ntiles[s] == 0) continue;
-    const int grid = B->shape.grid > 0 ? B->shape.grid : int(ln.tile_cap[s]);
     const int P = ln.nboxes[s] == 0 ? 0 : (B->pass_steps == 2 ? passes_in(nsteps) : auto_passes_in(nsteps));
-    for (int i = 0; i < P; ++i)
-      LBM_BHIP(lbm::launch_batch_pass(s, ln.d_lats, ln.d_boxes[s], ln.d_ntiles + kNumStorage + s, first + 2 * i, i & 1,
-                                      pass_planes(B), B->pass_remap, int(ln.box_cap[s]), ln.stream),
-               "batch pass launch");
-    // (the jobs with boxes: P, an even number of passes, then single steps;
-    // the others' buffers flip once a step)
-    for (int j = ln.nplain[s] > 0 ? 0 : 2 * P; j < nsteps; ++j) {
-      const bool all = j >= 2 * P;
-      LBM_BHIP(lbm::launch_batch_sweep(s, B->shape.block_x, ln.d_lats, ln.d_tiles[s],
-                                       ln.d_ntiles + (all ? 0 : 2 * kNumStorage) + s, first + j, j & 1,
-                                       measure && j == nsteps - 1 ? ln.d_part + ln.part_off[s] : nullptr, grid,
-                                       B->shape.grid == 0, ln.stream),
-               "batch sweep launch");
-    }
+    lbm_status st = launch_passes(B, ln, s, P, first);
+    if (st == LBM_OK) st = launch_singles(B, ln, s, P, 0, nsteps, first, measure);
+    if (st != LBM_OK) return st;
   }
   return LBM_OK;
 }
@@ -1862,8 +1879,17 @@ lbm_status lbm_batch_autotune(lbm_batch *B, int trial_steps, int *block_x, int *
     // orders (the single step's shape stays the default: chunks of a
     // multiple of 4 steps take no single step), timed over at least 4 steps
     // (2 passes), a multiple of 4, after 2 warm-up passes.
+    //
+    // Where jobs make passes by default, a candidate's steps are those of a
+    // chunk: the jobs with boxes make P passes (of the `timed` steps; none
+    // for 2) and the rest as single steps, the others single steps only.  The
+    // shape governs the single steps alone and is judged by their time; the
+    // passes are timed apart, in the two box orders by turns.
     const int warm = pass2 ? 4 : 2;
     const int timed = pass2 ? (std::max(trial_steps, 4) + 3) / 4 * 4 : trial_steps;
+    bool boxes = false;
+    for (int s = 0; s < kNumStorage; ++s) boxes = boxes || ln.nboxes[s] > 0;
+    const int P = !pass2 && boxes ? passes_in(timed) : 0;
     std::vector<Tuned> cands;
     if (pass2) {
       for (int zc : {16, 32, 64})
@@ -1872,38 +1898,56 @@ lbm_status lbm_batch_autotune(lbm_batch *B, int trial_steps, int *block_x, int *
       // one workgroup per tile of 256-1024 nodes, and two persistent grids
       for (const Shape &c : {Shape{256, 256, 0}, Shape{256, 512, 0}, Shape{256, 1024, 0}, Shape{128, 256, 0},
                              Shape{256, 1024, 16 * B->num_cu}, Shape{128, 1024, 8 * B->num_cu}})
-        cands.push_back({c, B->pass_zc, B->pass_remap});
+        cands.push_back({c, B->pass_zc, P > 0 ? int(1 - cands.size() % 2) : B->pass_remap});
     }
-    hipEvent_t e0, e1;
-    LBM_BHIP(hipEventCreate(&e0), "event");
-    LBM_BHIP(hipEventCreate(&e1), "event");
+    hipEvent_t ev[4];  // passes from 0 to 1, warm-up from 1 to 2, timed single steps from 2 to 3
+    for (hipEvent_t &e : ev) LBM_BHIP(hipEventCreate(&e), "event");
     Tuned best;
-    float best_ms = INFINITY;
+    float best_ms = INFINITY, pass_ms[2] = {INFINITY, INFINITY};
     for (const Tuned &c : cands) {
       st = lbm_batch_set_shape(B, c.shape.block_x, c.shape.tile_nodes, c.shape.grid);
       B->pass_zc = c.zc;
       B->pass_remap = c.remap;
       if (st == LBM_OK) st = upload_tables(B, ln, all);
-      if (st == LBM_OK) st = launch_steps(B, ln, warm, 0, false);
-      hipError_t e = st == LBM_OK ? hipEventRecord(e0, ln.stream) : hipSuccess;
-      if (st == LBM_OK && e == hipSuccess) st = launch_steps(B, ln, timed, warm, false);
-      if (st == LBM_OK && e == hipSuccess) e = hipEventRecord(e1, ln.stream);
-      if (st == LBM_OK && e == hipSuccess) e = hipEventSynchronize(e1);
-      float ms = 0.f;
-      if (st == LBM_OK && e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+      hipError_t e = hipSuccess;
+      auto each_form = [&](auto launch) {
+        for (int s = 0; s < kNumStorage && st == LBM_OK; ++s)
+          if (ln.ntiles[s] > 0) st = launch(s, ln.nboxes[s] > 0 ? P : 0);
+      };
+      auto record = [&](int i) {
+        if (st == LBM_OK && e == hipSuccess) e = hipEventRecord(ev[i], ln.stream);
+      };
+      if (P > 0) {
+        const int n = warm + timed;
+        record(0);
+        each_form([&](int s, int p) { return launch_passes(B, ln, s, p, 0); });
+        record(1);
+        each_form([&](int s, int p) { return launch_singles(B, ln, s, p, 0, warm, 0, false); });
+        record(2);
+        each_form([&](int s, int p) { return launch_singles(B, ln, s, p, warm, n, 0, false); });
+      } else {
+        if (st == LBM_OK) st = launch_steps(B, ln, warm, 0, false);
+        record(2);
+        if (st == LBM_OK) st = launch_steps(B, ln, timed, warm, false);
+      }
+      record(3);
+      if (st == LBM_OK && e == hipSuccess) e = hipEventSynchronize(ev[3]);
+      float ms = 0.f, pms = INFINITY;
+      if (st == LBM_OK && e == hipSuccess) e = hipEventElapsedTime(&ms, ev[2], ev[3]);
+      if (P > 0 && st == LBM_OK && e == hipSuccess) e = hipEventElapsedTime(&pms, ev[0], ev[1]);
       if (st != LBM_OK || e != hipSuccess) {
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
+        for (hipEvent_t x : ev) (void)hipEventDestroy(x);
         return st != LBM_OK ? st : bfail(LBM_ERR_HIP, "autotune timing: %s", hipGetErrorString(e));
       }
       for (int slot : all) B->jobs.at(B->slot_job[slot]).steps += warm + timed;
+      if (c.remap == 0 || c.remap == 1) pass_ms[c.remap] = std::min(pass_ms[c.remap], pms);
       if (ms < best_ms) {
         best_ms = ms;
         best = c;
       }
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
+    for (hipEvent_t x : ev) (void)hipEventDestroy(x);
+    if (P > 0) best.remap = pass_ms[0] < pass_ms[1] ? 0 : 1;
     {
       std::lock_guard<std::mutex> lock(g_tuned_mutex);
       g_tuned[key] = best;
@@ -1930,6 +1974,13 @@ lbm_status lbm_batch_get_stats(const lbm_batch *B, lbm_batch_stats *stats) {
   if (!B || !stats) return bfail(LBM_ERR_ARG, "NULL argument");
   *stats = B->stats;
   return LBM_OK;
+}
+
+// For the tests: passes of two steps enqueued by the batch's multi-lattice
+// kernel so far (a captured chunk's count once), and the box order of the next.
+void lbm_internal_batch_passes(const lbm_batch *B, long long *launches, int *box_order) {
+  *launches = B->pass_launches;
+  *box_order = B->pass_remap;
 }
 
 }  // extern "C"

@@ -1,6 +1,8 @@
 """lbm_batch_autotune: a batch takes over the shape tuned for an earlier one only
 if it holds the same kind of work (storage forms and how they step, resident
 nodes to a power of two)."""
+import ctypes
+
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -91,3 +93,40 @@ def test_padding_only_where_steps_are_grouped(jobs, padded, lanes):
     if len(jobs) == 100:
         jobs = [(40, 70, 16)] * 300 if lanes == 4 else jobs[:25]  # 3000 and 1000 boxes
     assert _padded(jobs, 100, lanes) == padded
+
+
+def _passes(b):
+    launches, order = ctypes.c_longlong(), ctypes.c_int()
+    ctypes.CDLL(lbm.LIB_PATH).lbm_internal_batch_passes(ctypes.c_void_p(b), ctypes.byref(launches), ctypes.byref(order))
+    return launches.value
+
+
+# (each mix of forms is tuned once in a process)
+@pytest.mark.parametrize("trial, small", [(2, ["f16sr"]), (4, ["f16dev"]), (6, ["f16sr", "f16dev"]), (16, [])])
+def test_tuning_times_the_passes_of_a_default_batch(trial, small):
+    """Of the trial steps the jobs that make passes in a chunk make them too;
+    the number of steps and the state do not depend on that."""
+    items = [(workloads.duct(128, 98, 113, (0.03, 0.01, 0.0), 0.9), "f64"),
+             (workloads.duct(127, 98, 100, (0.02, 0.01, 0.01), 0.8), "f64"),
+             (workloads.duct(33, 20, 30, (0.02, 0.01, 0.01), 0.8), "f64"),
+             (workloads.duct(256, 156, 160, (0.03, 0.0, 0.01), 0.9), "f32")]
+    items += [(workloads.duct(33, 20, 22, (0.02, 0.01, 0.01), 0.8), st) for st in small]
+    got = []
+    for tune in (True, False):
+        steps = 6 * (2 + trial)
+        b = lbm.lbm_batch_create(4 << 30, 6 if tune else steps + 6, 8)
+        try:
+            if not tune:
+                lbm.lbm_batch_set_steps_per_pass(b, 1)
+            ids = [lbm.lbm_batch_submit(b, serving.job_for(s, st, 0.0, steps + 6)) for s, st in items]
+            if tune:
+                lbm.lbm_batch_autotune(b, trial)
+                assert [lbm.lbm_batch_poll(b, i).steps for i in ids] == [steps] * len(items)
+                assert (_passes(b) > 0) == (trial >= 4)
+            while lbm.lbm_batch_run_chunk(b) != (0, 0):
+                pass
+            got.append([lbm.lbm_batch_result(b, i, s.nodes) for i, (s, _) in zip(ids, items)])
+        finally:
+            lbm.lbm_batch_destroy(b)
+    for (s, st), (rho, u), (r, v) in zip(items, *got):
+        assert (rho == r).all() and (u == v).all(), (s.name, st)
