@@ -323,8 +323,10 @@ enum { LBM_XCD_NONE = 0, LBM_XCD_SLABS = 1, LBM_XCD_ROWS = 2 };
 
 /* Launch shape of the sweep kernel: block_x threads along x (64, 128, 256 or
  * 512), nodes_per_thread along x (1, 2 or 4), xcd_remap one of LBM_XCD_*.
- * Any shape gives the same results.  Errors: LBM_ERR_ARG for an unsupported
- * shape. */
+ * Any shape gives the same results.  After this call every step of lbm_step
+ * is a launch of its own (unless two steps per pass are set), also on small
+ * lattices, which as created make several steps per launch.  Errors:
+ * LBM_ERR_ARG for an unsupported shape. */
 lbm_status lbm_set_launch(lbm_lattice *L, int block_x, int nodes_per_thread, int xcd_remap);
 lbm_status lbm_get_launch(const lbm_lattice *L, int *block_x, int *nodes_per_thread, int *xcd_remap);
 
@@ -347,12 +349,14 @@ lbm_status lbm_get_launch(const lbm_lattice *L, int *block_x, int *nodes_per_thr
  * the form's default; 5, five-row tiles (two workgroups per compute unit);
  * 12, twelve-row tiles (15 waves, three of step 2's 12 on each SIMD; within
  * 4% of 13 rows either way); FP64 tiles have seven rows either way.  Every variant
- * gives the same bits.  steps_per_pass = 1: one single sweep per step (the
- * default); small lattices (up to about 65000 nodes, without those options)
- * make two or three steps per launch, and until this call, lbm_set_launch or
- * lbm_autotune chooses the launch, larger row-major ones make passes where
- * they are estimated to be faster -- with the same bits, in the buffer that
- * single steps end in.  Errors: LBM_ERR_ARG (NULL, steps_per_pass not 1 or 2,
+ * gives the same bits.  A z plane of 4 GiB or more (28 million FP64 or 56
+ * million FP32 nodes) takes single sweeps instead.  steps_per_pass = 1: one
+ * single sweep per step.  As created, a lattice has one step per pass, but
+ * until this call, lbm_set_launch or lbm_autotune chooses the launch, small
+ * lattices (up to about 65000 nodes, without those options) make two or three
+ * steps per launch and larger row-major ones make passes where they are
+ * estimated to be faster -- with the same bits, in the buffer that single
+ * steps end in.  Errors: LBM_ERR_ARG (NULL, steps_per_pass not 1 or 2,
  * z_planes < 0, tile_rows not 0, 5 or 12). */
 lbm_status lbm_set_steps_per_pass(lbm_lattice *L, int steps_per_pass, int z_planes, int tile_rows);
 lbm_status lbm_get_steps_per_pass(const lbm_lattice *L, int *steps_per_pass, int *z_planes, int *tile_rows);
@@ -372,10 +376,13 @@ lbm_status lbm_get_step(const lbm_lattice *L, unsigned long long *steps);
  * the device's compute units, or 64, tiles of the form's default rows, 5 or
  * 12 rows (FP64: its 7 only), slab or dispatch-order placement) one untimed
  * and trial_steps timed pairs, on the lattice's stream (HIP events, compared
- * per step).  The steps are part of the run (results do not depend
- * on the choice).  Sets the winner -- launch shape, steps per pass, z range
- * and tile rows -- and returns the launch shape through the non-NULL
- * pointers (lbm_get_steps_per_pass gives the rest).  Synchronizes.  Errors:
+ * per step); for a small lattice, the launches of several steps that it makes
+ * as created are a candidate too (timed without advancing it).  The steps are
+ * part of the run (results do not depend on the choice).  Sets the winner --
+ * launch shape, steps per pass, z range and tile rows, or those launches -- and
+ * returns the launch shape through the non-NULL pointers
+ * (lbm_get_steps_per_pass gives the rest; lbm_set_launch with the values
+ * returned gives single sweeps).  Synchronizes.  Errors:
  * LBM_ERR_ARG, LBM_ERR_STATE (as lbm_step), LBM_ERR_HIP; on error the
  * previous settings are restored. */
 lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *nodes_per_thread, int *xcd_remap);

@@ -84,6 +84,7 @@ struct lbm_lattice {
   int block_x, npt, xcd;
   int pass_steps;  // 1 or 2 steps per pass over HBM
   bool pass_auto;  // neither the steps per pass nor the launch shape chosen by the caller or lbm_autotune
+  bool blocks;     // a small lattice makes several steps per launch: as created, or lbm_autotune's choice
   int compute_units;
   int zc;          // z-planes per workgroup of the two-step pass
   int tile_rows;   // interior rows of its tiles (0: the form's default)
@@ -142,6 +143,7 @@ static void default_launch(lbm_lattice *L) {
   L->zc = kDefaultZPlanes;
   L->tile_rows = 0;
   L->pass_auto = true;
+  L->blocks = true;
   L->compute_units = lbm::device_compute_units();
 }
 
@@ -472,6 +474,41 @@ static lbm::SweepConfig sweep_config(const lbm_lattice *L) {
   return c;
 }
 
+static bool extended(const lbm_lattice *L) {
+  return L->d_solid || L->d_geo || L->d_face_v[0] || L->d_face_v[1] || L->d_face_v[2] || L->d_face_v[3] ||
+         L->d_face_v[4] || L->d_face_v[5];
+}
+
+// Launches of lbm_step(nsteps): `groups` of `group` steps each -- passes of two
+// with z ranges of zc planes and tile_rows, or, zc 0, blocks of steps -- then
+// single sweeps.
+struct StepPlan {
+  int group, groups, zc, tile_rows;
+};
+
+// With two steps per pass set, passes.  With one, small lattices by blocks of
+// steps and larger ones by passes where they pay, as long as the caller has
+// chosen no launch (or lbm_autotune found the blocks fastest).  Launches of an
+// even number of steps then come in pairs, so that the state alternates between
+// the buffers as with single steps.
+static StepPlan step_plan(const lbm_lattice *L, const lbm::SweepConfig &c, int nsteps) {
+  StepPlan p{1, 0, 0, 0};
+  if (extended(L)) return p;
+  if (L->pass_steps == 2) {
+    if (lbm::sweep2_takes(L->lay, L->ny, L->storage)) p = {2, nsteps / 2, L->zc, L->tile_rows};
+    return p;
+  }
+  const int block = L->blocks ? lbm::block_steps(c) : 0;
+  if (block > 0) {
+    p = {block, nsteps / block, 0, 0};
+  } else if (L->pass_auto && nsteps >= 4) {
+    const int zc = lbm::sweep2_pays(c, L->compute_units);
+    if (zc > 0) p = {2, nsteps / 2, zc, 0};
+  }
+  if (p.group == 2) p.groups &= ~1;
+  return p;
+}
+
 lbm_status lbm_step(lbm_lattice *L, int nsteps) {
   if (!L) return fail(LBM_ERR_ARG, "NULL handle");
   if (nsteps < 0) return fail(LBM_ERR_ARG, "nsteps must be >= 0");
@@ -488,30 +525,17 @@ lbm_status lbm_step(lbm_lattice *L, int nsteps) {
   if (p_axes > 1)
     return fail(LBM_ERR_STATE, "pressure faces on %d axes: edges between two pressure faces are not defined", p_axes);
   lbm::SweepConfig c = sweep_config(L);
-  const bool ext = L->d_solid || L->d_geo || L->d_face_v[0] || L->d_face_v[1] || L->d_face_v[2] ||
-                   L->d_face_v[3] || L->d_face_v[4] || L->d_face_v[5];
-  const bool two = L->pass_steps == 2 && lbm::sweep2_takes(L->lay, L->ny, L->storage) && !ext;
-  // With one step per pass: small lattices by blocks of steps, and, as long as
-  // the caller has chosen no launch, larger ones by passes where they pay.
-  // Launches of an even number of steps then come in pairs, so that the state
-  // alternates between the buffers as with single steps.
-  const int block = L->pass_steps == 1 && !ext ? lbm::block_steps(c) : 0;
-  const int auto_zc = L->pass_steps == 1 && !ext && block == 0 && L->pass_auto && nsteps >= 4
-                          ? lbm::sweep2_pays(c, L->compute_units)
-                          : 0;
-  const int group = two || auto_zc > 0 ? 2 : block;
-  int groups = group > 0 ? nsteps / group : 0;  // launches of `group` steps; then single steps
-  if (!two && group == 2) groups &= ~1;
+  const StepPlan p = step_plan(L, c, nsteps);
+  int groups = p.groups;
   for (int s = 0; s < nsteps;) {
     c.step = unsigned(L->steps);
     c.solids_kept = s > 0;  // copied by the first step of this call
-    const int n = groups-- > 0 ? group : 1;
+    const int n = groups-- > 0 ? p.group : 1;
     const void *from = L->buf[L->cur];
     void *to = L->buf[L->cur ^ 1];
-    const hipError_t e = n == 1   ? lbm::launch_sweep(c, from, to, false, L->stream)
-                         : two    ? lbm::launch_sweep2(c, L->zc, L->tile_rows, from, to, L->stream)
-                         : auto_zc > 0 ? lbm::launch_sweep2(c, auto_zc, 0, from, to, L->stream)
-                                  : lbm::launch_block_steps(c, from, to, L->stream);
+    const hipError_t e = n == 1     ? lbm::launch_sweep(c, from, to, false, L->stream)
+                         : p.zc > 0 ? lbm::launch_sweep2(c, p.zc, p.tile_rows, from, to, L->stream)
+                                    : lbm::launch_block_steps(c, from, to, L->stream);
     if (e != hipSuccess) return hip_fail(e, n == 1 ? "sweep launch" : "launch of several steps");
     L->cur ^= 1;
     L->steps += unsigned(n);
@@ -654,7 +678,7 @@ lbm_status lbm_set_launch(lbm_lattice *L, int block_x, int nodes_per_thread, int
   L->block_x = block_x;
   L->npt = nodes_per_thread;
   L->xcd = xcd_remap;
-  L->pass_auto = false;
+  L->pass_auto = L->blocks = false;
   return LBM_OK;
 }
 
@@ -673,7 +697,7 @@ lbm_status lbm_set_steps_per_pass(lbm_lattice *L, int steps_per_pass, int z_plan
   if (z_planes < 0) return fail(LBM_ERR_ARG, "z_planes must be >= 0 (got %d)", z_planes);
   if (tile_rows != 0 && tile_rows != 5 && tile_rows != 12)
     return fail(LBM_ERR_ARG, "tile_rows must be 0, 5 or 12 (got %d)", tile_rows);
-  L->pass_auto = false;
+  L->pass_auto = L->blocks = false;
   L->pass_steps = steps_per_pass;
   L->zc = z_planes == 0 ? kDefaultZPlanes : z_planes;
   L->tile_rows = tile_rows;
@@ -711,13 +735,13 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
   // rounded up to a power of two (at least 64); one node per thread for the
   // extended sweep.  In the row-major layout without extended options also
   // the two-step pass: several z ranges, tiles of the form's default rows, 5
-  // or 12 rows, slab or dispatch-order placement.
-  const bool ext = L->d_solid || L->d_geo || L->d_face_v[0] || L->d_face_v[1] || L->d_face_v[2] ||
-                   L->d_face_v[3] || L->d_face_v[4] || L->d_face_v[5];
+  // or 12 rows, slab or dispatch-order placement.  For a small lattice also
+  // its blocks of steps.
+  const bool ext = extended(L);
   int row = 64;
   while (row < L->nx && row < 512) row *= 2;
   struct Cand {
-    int pass, bx, npt, xcd, zc, rows;
+    int pass, bx, npt, xcd, zc, rows;  // pass 0: blocks of steps
   };
   std::vector<Cand> cands;
   static const int shape[][2] = {{64, 1}, {128, 1}, {256, 1}, {512, 1}, {128, 2}, {256, 2}, {128, 4}, {256, 4}};
@@ -742,13 +766,16 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
       for (int zc : zcs)
         for (int xcd : {LBM_XCD_SLABS, LBM_XCD_NONE}) cands.push_back({2, L->block_x, L->npt, xcd, zc, rows});
     }
-  const bool old_auto = L->pass_auto;
-  L->pass_auto = false;
+  const int block = ext ? 0 : lbm::block_steps(sweep_config(L));
+  if (block > 0) cands.push_back({0, L->block_x, L->npt, L->xcd, 0, 0});
+  const bool old_auto = L->pass_auto, old_blocks = L->blocks;
+  L->pass_auto = L->blocks = false;
   const int old[6] = {L->block_x, L->npt, L->xcd, L->pass_steps, L->zc, L->tile_rows};
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     if (e0) (void)hipEventDestroy(e0);
     L->pass_auto = old_auto;
+    L->blocks = old_blocks;
     return hip_fail(hipGetLastError(), "event creation");
   }
   float best_ms = 0.0f;
@@ -759,15 +786,26 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
     L->block_x = c.bx;
     L->npt = c.npt;
     L->xcd = c.xcd;
-    L->pass_steps = c.pass;
+    L->pass_steps = c.pass == 2 ? 2 : 1;
     L->zc = c.pass == 2 ? c.zc : old[4];
     L->tile_rows = c.pass == 2 ? c.rows : old[5];
-    // untimed launches, then timed ones (all of them real steps); the pass
-    // takes pairs of steps
-    const int n = c.pass == 2 ? 2 * trial_steps : trial_steps;
-    result = lbm_step(L, c.pass);
+    // Untimed launches, then timed ones, all of them real steps; the pass
+    // takes pairs of steps.  The blocks are no steps: every launch takes the
+    // state into the other buffer, which nothing reads (so the count of trial
+    // steps does not depend on them), at least 8 times, as a launch is short.
+    const int launches = c.pass == 0 ? std::max(trial_steps, 8) : 0;
+    const int n = c.pass == 0 ? block * launches : c.pass * trial_steps;
+    auto take = [&](int steps, int blocks) {
+      const lbm::SweepConfig sc = sweep_config(L);
+      for (int b = 0; b < blocks; ++b) {
+        const hipError_t e = lbm::launch_block_steps(sc, L->buf[L->cur], L->buf[L->cur ^ 1], L->stream);
+        if (e != hipSuccess) return hip_fail(e, "launch of several steps");
+      }
+      return blocks > 0 ? LBM_OK : lbm_step(L, steps);
+    };
+    result = take(c.pass, launches > 0 ? 1 : 0);
     if (result == LBM_OK && hipEventRecord(e0, L->stream) != hipSuccess) result = hip_fail(hipGetLastError(), "event");
-    if (result == LBM_OK) result = lbm_step(L, n);
+    if (result == LBM_OK) result = take(n, launches);
     if (result == LBM_OK && hipEventRecord(e1, L->stream) != hipSuccess) result = hip_fail(hipGetLastError(), "event");
     float ms = 0.0f;
     if (result == LBM_OK && hipEventSynchronize(e1) != hipSuccess) result = hip_fail(hipGetLastError(), "event");
@@ -789,13 +827,15 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
     L->zc = old[4];
     L->tile_rows = old[5];
     L->pass_auto = old_auto;
+    L->blocks = old_blocks;
     return result != LBM_OK ? result : fail(LBM_ERR_STATE, "no launch shape to try");
   }
   const Cand &c = cands[best];
   L->block_x = c.bx;
   L->npt = c.npt;
   L->xcd = c.xcd;
-  L->pass_steps = c.pass;
+  L->pass_steps = c.pass == 2 ? 2 : 1;
+  L->blocks = c.pass == 0;
   L->zc = c.pass == 2 ? c.zc : old[4];
   L->tile_rows = c.pass == 2 ? c.rows : old[5];
   if (block_x) *block_x = L->block_x;
@@ -914,6 +954,14 @@ lbm_status lbm_probe(lbm_lattice *L, int kind, int nrep) {
     if (e != hipSuccess) return hip_fail(e, "probe launch");
   }
   return LBM_OK;
+}
+
+// For the tests: the launches lbm_step(nsteps) would make.
+void lbm_internal_step_plan(const lbm_lattice *L, int nsteps, int *group, int *groups, int *z_planes) {
+  const StepPlan p = step_plan(L, sweep_config(L), nsteps);
+  *group = p.group;
+  *groups = p.groups;
+  *z_planes = p.zc;
 }
 
 }  // extern "C"

@@ -1,0 +1,78 @@
+"""Which launches lbm_step makes: as created, after the caller chose a launch and
+after lbm_autotune, and the same bits each way."""
+import ctypes
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_0811_4593_amd import lbm, serving, workloads  # noqa: E402
+
+STORAGES = [lbm.LBM_STORE_F64, lbm.LBM_STORE_F32, lbm.LBM_STORE_F16_DEV, lbm.LBM_STORE_F16_DEV_SR]
+W = np.array([1 / 18] * 6 + [1 / 36] * 12 + [1 / 3])[:, None, None, None]
+
+
+def plan(h, nsteps):
+    """Steps of a grouped launch (1: none), such launches, z planes of a pass (0: blocks of steps)."""
+    out = [ctypes.c_int() for _ in range(3)]
+    ctypes.CDLL(lbm.LIB_PATH).lbm_internal_step_plan(ctypes.c_void_p(h), nsteps, *map(ctypes.byref, out))
+    return tuple(v.value for v in out)
+
+
+def make(spec, storage):
+    h = lbm.lbm_create(spec.nx, spec.ny, spec.nz, spec.tau, 1.0, None, storage, torch.cuda.current_stream())
+    serving.apply_bc(h, spec)
+    lbm.lbm_set_populations(h, W * workloads.perturbation((19, spec.nz, spec.ny, spec.nx), 5, 0.05))
+    return h
+
+
+def state(h, spec):
+    out = np.empty((19, spec.nz, spec.ny, spec.nx))
+    lbm.lbm_get_populations(h, out)
+    return out
+
+
+SMALL = workloads.duct(17, 16, 16, (0.03, -0.02, 0.01), 0.8)
+LARGE = workloads.duct(128, 96, 96, (0.04, 0.01, 0.01), 0.8)
+
+
+def test_a_chosen_launch_takes_one_step_per_launch():
+    for spec, group in ((SMALL, 3), (LARGE, 2)):
+        h = make(spec, lbm.LBM_STORE_F64)
+        try:
+            assert plan(h, 30)[0] == group
+            lbm.lbm_set_launch(h, 64, 1, lbm.LBM_XCD_NONE)
+            assert plan(h, 30) == (1, 0, 0)
+            lbm.lbm_set_steps_per_pass(h, 2, 16)
+            assert plan(h, 31) == (2, 15, 16)
+        finally:
+            lbm.lbm_destroy(h)
+        h = make(spec, lbm.LBM_STORE_F64)
+        try:
+            lbm.lbm_set_steps_per_pass(h, 1)
+            assert plan(h, 30) == (1, 0, 0)
+        finally:
+            lbm.lbm_destroy(h)
+
+
+@pytest.mark.parametrize("trial, steps", [(1, 28), (2, 42)])
+def test_autotune_of_a_small_lattice(trial, steps):
+    """Blocks of steps are a candidate (3.1 against 4.6 us per step) that takes no
+    trial step, and the state after the trial steps is that of single sweeps."""
+    h, g = make(SMALL, lbm.LBM_STORE_F64), make(SMALL, lbm.LBM_STORE_F64)
+    try:
+        lbm.lbm_autotune(h, trial)
+        assert lbm.lbm_get_step(h) == steps
+        assert plan(h, 30) == (3, 10, 0)
+        lbm.lbm_step(h, 30)
+        for _ in range(steps + 30):
+            lbm.lbm_step(g, 1)
+        np.testing.assert_array_equal(state(h, SMALL), state(g, SMALL))
+    finally:
+        lbm.lbm_destroy(h)
+        lbm.lbm_destroy(g)
