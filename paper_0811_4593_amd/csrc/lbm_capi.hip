@@ -88,6 +88,7 @@ struct lbm_lattice {
   int compute_units;
   int zc;          // z-planes per workgroup of the two-step pass
   int tile_rows;   // interior rows of its tiles (0: the form's default)
+  long long grouped;         // launches of several steps lbm_step has made
   unsigned long long steps;  // steps taken since creation (its low 32 bits key the stochastic rounding)
   double *d_partials;  // [kPartialBlocks * 4]
   double *d_totals;    // [4]
@@ -539,6 +540,7 @@ lbm_status lbm_step(lbm_lattice *L, int nsteps) {
     if (e != hipSuccess) return hip_fail(e, n == 1 ? "sweep launch" : "launch of several steps");
     L->cur ^= 1;
     L->steps += unsigned(n);
+    L->grouped += n > 1;
     s += n;
   }
   return LBM_OK;
@@ -879,8 +881,16 @@ lbm_status lbm_tune_placement(lbm_lattice *L, int max_buffers, int trial_steps, 
     result = hip_fail(hipGetLastError(), "event creation");
   }
   // Every unordered pair (i, j), i < j, with the state in pool[i]: two
-  // untimed and 2 * trial_steps timed steps (an even count, so the state is
-  // back in pool[i]).  L->buf always holds the state buffer and its partner.
+  // untimed and 2 * trial_steps timed steps, by the kernel that a long lbm_step
+  // call runs: passes of two steps where it makes them without being asked.
+  // L->buf always holds the state buffer and its partner.
+  const int old[3] = {L->pass_steps, L->zc, L->tile_rows};
+  const StepPlan run = step_plan(L, sweep_config(L), 4);
+  if (run.zc > 0) {
+    L->pass_steps = 2;
+    L->zc = run.zc;
+    L->tile_rows = run.tile_rows;
+  }
   float first_ms = -1.0f, best_ms = 0.0f;
   int bi = 0, bj = 1;
   for (int i = 0; i + 1 < n && result == LBM_OK; ++i) {
@@ -913,6 +923,9 @@ lbm_status lbm_tune_placement(lbm_lattice *L, int max_buffers, int trial_steps, 
       }
     }
   }
+  L->pass_steps = old[0];
+  L->zc = old[1];
+  L->tile_rows = old[2];
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (result == LBM_OK) {
@@ -956,12 +969,15 @@ lbm_status lbm_probe(lbm_lattice *L, int kind, int nrep) {
   return LBM_OK;
 }
 
-// For the tests: the launches lbm_step(nsteps) would make.
-void lbm_internal_step_plan(const lbm_lattice *L, int nsteps, int *group, int *groups, int *z_planes) {
+// For the tests: the launches lbm_step(nsteps) would make, and the launches of
+// several steps it has made so far.
+void lbm_internal_step_plan(const lbm_lattice *L, int nsteps, int *group, int *groups, int *z_planes,
+                            long long *grouped) {
   const StepPlan p = step_plan(L, sweep_config(L), nsteps);
   *group = p.group;
   *groups = p.groups;
   *z_planes = p.zc;
+  *grouped = L->grouped;
 }
 
 }  // extern "C"

@@ -17,11 +17,20 @@ STORAGES = [lbm.LBM_STORE_F64, lbm.LBM_STORE_F32, lbm.LBM_STORE_F16_DEV, lbm.LBM
 W = np.array([1 / 18] * 6 + [1 / 36] * 12 + [1 / 3])[:, None, None, None]
 
 
-def plan(h, nsteps):
-    """Steps of a grouped launch (1: none), such launches, z planes of a pass (0: blocks of steps)."""
-    out = [ctypes.c_int() for _ in range(3)]
+def _internal(h, nsteps):
+    out = [ctypes.c_int() for _ in range(3)] + [ctypes.c_longlong()]
     ctypes.CDLL(lbm.LIB_PATH).lbm_internal_step_plan(ctypes.c_void_p(h), nsteps, *map(ctypes.byref, out))
     return tuple(v.value for v in out)
+
+
+def plan(h, nsteps):
+    """Steps of a grouped launch (1: none), such launches, z planes of a pass (0: blocks of steps)."""
+    return _internal(h, nsteps)[:3]
+
+
+def grouped(h):
+    """Launches of several steps so far."""
+    return _internal(h, 0)[3]
 
 
 def make(spec, storage):
@@ -73,6 +82,26 @@ def test_autotune_of_a_small_lattice(trial, steps):
         for _ in range(steps + 30):
             lbm.lbm_step(g, 1)
         np.testing.assert_array_equal(state(h, SMALL), state(g, SMALL))
+    finally:
+        lbm.lbm_destroy(h)
+        lbm.lbm_destroy(g)
+
+
+@pytest.mark.parametrize("trial", [1, 2])
+def test_placement_is_timed_with_the_passes_that_run(trial):
+    h, g = make(LARGE, lbm.LBM_STORE_F64), make(LARGE, lbm.LBM_STORE_F64)
+    try:
+        before = plan(h, 30)
+        assert before[0] == 2 and before[2] > 0
+        tried, _, _ = lbm.lbm_tune_placement(h, 3, trial)
+        pairs = tried * (tried - 1) // 2
+        assert lbm.lbm_get_step(h) == pairs * (2 + 2 * trial)
+        assert grouped(h) == pairs * (1 + trial)
+        assert plan(h, 30) == before and lbm.lbm_get_steps_per_pass(h)[0] == 1
+        lbm.lbm_step(h, 7)
+        for _ in range(lbm.lbm_get_step(h)):
+            lbm.lbm_step(g, 1)
+        np.testing.assert_array_equal(state(h, LARGE), state(g, LARGE))
     finally:
         lbm.lbm_destroy(h)
         lbm.lbm_destroy(g)
