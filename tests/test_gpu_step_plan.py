@@ -105,3 +105,113 @@ def test_placement_is_timed_with_the_passes_that_run(trial):
     finally:
         lbm.lbm_destroy(h)
         lbm.lbm_destroy(g)
+
+
+INT_OF = {8: torch.int64, 4: torch.int32, 2: torch.int16}
+DTYPE = {lbm.LBM_STORE_F64: torch.float64, lbm.LBM_STORE_F32: torch.float32, lbm.LBM_STORE_F16_DEV: torch.float16,
+         lbm.LBM_STORE_F16_DEV_SR: torch.float16}
+
+
+class OnDevice:
+    """A row-major lattice on torch buffers with a random state (populations in
+    units of their weights, 5% up and down)."""
+
+    def __init__(self, spec, storage):
+        esize = lbm.lbm_element_bytes(storage)
+        n = lbm.lbm_buffer_elements(spec.nx, spec.ny, spec.nz, storage, lbm.LBM_LAYOUT_ROW_MAJOR)
+        n = max(n, lbm.lbm_buffer_elements(spec.nx, spec.ny, spec.nz, storage, lbm.LBM_LAYOUT_POPULATION_MAJOR))
+        self.pitch = lbm.lbm_buffer_elements(spec.nx, 1, 1, storage, lbm.LBM_LAYOUT_ROW_MAJOR) // 19
+        self.spec = spec
+        self.bufs = [torch.zeros(n, dtype=DTYPE[storage], device="cuda") for _ in range(2)]
+        self.h = lbm.lbm_create_on_buffers(spec.nx, spec.ny, spec.nz, spec.tau, 1.0, None, storage,
+                                           torch.cuda.current_stream(), *self.bufs, n * esize)
+        lbm.lbm_set_layout(self.h, lbm.LBM_LAYOUT_ROW_MAJOR)
+        serving.apply_bc(self.h, spec)
+        v = self.state()
+        g = torch.Generator(device="cuda")
+        for k in range(19):
+            g.manual_seed(k)
+            for z in range(spec.nz):
+                t = torch.rand(spec.ny, spec.nx, generator=g, device="cuda", dtype=torch.float32)
+                v[z, :, k].copy_((t - 0.5) * (0.1 * float(W[k].item()) * (256.0 if esize == 2 else 1.0)))
+
+    def which(self):
+        return int(lbm.lbm_state_buffer(self.h) != self.bufs[0].data_ptr())
+
+    def state(self):
+        s = self.spec
+        b = self.bufs[self.which()]
+        return b[: 19 * self.pitch * s.ny * s.nz].view(s.nz, s.ny, 19, self.pitch)[..., : s.nx]
+
+    def close(self):
+        lbm.lbm_destroy(self.h)
+        self.bufs = None
+
+
+def same_state(a, b):
+    torch.cuda.synchronize()
+    x, y = a.state(), b.state()
+    i = INT_OF[x.element_size()]
+    return all(torch.equal(x[z].view(i), y[z].view(i)) for z in range(a.spec.nz))
+
+
+@pytest.mark.parametrize("spec, storage", [
+    (LARGE, lbm.LBM_STORE_F64),
+    (LARGE, lbm.LBM_STORE_F32),
+    (workloads.duct(250, 130, 96, (0.04, 0.01, 0.01), 0.8), lbm.LBM_STORE_F32),
+    (workloads.duct(256, 208, 384, (0.04, 0.01, 0.01), 0.8), lbm.LBM_STORE_F16_DEV),
+    (workloads.duct(256, 208, 384, (0.04, 0.01, 0.01), 0.8), lbm.LBM_STORE_F16_DEV_SR),
+], ids=lambda v: v.name if hasattr(v, "name") else lbm.STORAGE_NAMES[v])
+def test_passes_as_created_equal_single_sweeps(spec, storage):
+    a, b = OnDevice(spec, storage), OnDevice(spec, storage)
+    try:
+        for n, pairs in ((5, 2), (8, 4), (3, 0)):
+            assert plan(a.h, n)[0] == (2 if n >= 4 else 1)
+            was = grouped(a.h)
+            lbm.lbm_step(a.h, n)
+            assert grouped(a.h) - was == pairs
+            for _ in range(n):
+                lbm.lbm_step(b.h, 1)
+            assert grouped(b.h) == 0
+            assert a.which() == b.which() and same_state(a, b), (spec.name, n)
+    finally:
+        a.close()
+        b.close()
+
+
+@pytest.mark.parametrize("nx, ny, nz, storage", [(4000, 4100, 4, lbm.LBM_STORE_F64), (8000, 8200, 4, lbm.LBM_STORE_F16_DEV_SR)],
+                         ids=["f64", "f16sr"])
+def test_pass_over_planes_above_2_gib(nx, ny, nz, storage):
+    """The pass addresses a z plane by 32-bit offsets, here with their top bit in use."""
+    spec = workloads.duct(nx, ny, nz, (0.03, 0.01, 0.01), 0.8)
+    a, b = OnDevice(spec, storage), OnDevice(spec, storage)
+    try:
+        assert 2 ** 31 < 19 * a.pitch * ny * a.bufs[0].element_size() < 2 ** 32
+        lbm.lbm_set_steps_per_pass(a.h, 2, 3)
+        lbm.lbm_set_steps_per_pass(b.h, 1)
+        lbm.lbm_step(a.h, 4)
+        lbm.lbm_step(b.h, 4)
+        assert (grouped(a.h), grouped(b.h)) == (2, 0)
+        assert same_state(a, b)
+    finally:
+        a.close()
+        b.close()
+
+
+def test_planes_of_4_gib_take_single_sweeps():
+    """Two steps per pass are accepted there, and the state is in the buffer that
+    single sweeps end in."""
+    spec = workloads.duct(4000, 7100, 3, (0.03, 0.01, 0.01), 0.8)
+    a = OnDevice(spec, lbm.LBM_STORE_F64)
+    try:
+        assert 19 * a.pitch * spec.ny * 8 >= 2 ** 32
+        was = a.which()
+        lbm.lbm_set_steps_per_pass(a.h, 2, 3)
+        assert plan(a.h, 4) == (1, 0, 0)
+        lbm.lbm_step(a.h, 2)
+        torch.cuda.synchronize()
+        assert grouped(a.h) == 0 and a.which() == was
+        mass, _ = lbm.lbm_totals(a.h)
+        assert abs(mass / spec.nodes - 1.0) < 1e-2
+    finally:
+        a.close()
