@@ -130,3 +130,34 @@ def test_tuning_times_the_passes_of_a_default_batch(trial, small):
             lbm.lbm_batch_destroy(b)
     for (s, st), (rho, u), (r, v) in zip(items, *got):
         assert (rho == r).all() and (u == v).all(), (s.name, st)
+
+
+@pytest.mark.parametrize("chunk", [6, 10, 50])
+@pytest.mark.parametrize("shape", [(256, 256, 0), (128, 1024, 64)], ids=["a-workgroup-per-tile", "persistent"])
+def test_shared_chunks_by_passes(chunk, shape):
+    """A lockstep batch whose larger jobs make passes (asserted) beside jobs that
+    do not, the convergence measure included, against single steps."""
+    items = [(workloads.duct(250, 130, 112, (0.03, 0.01, 0.0), 0.9), "f32"),
+             (workloads.duct(128, 117, 160, (0.03, 0.01, 0.0), 0.9), "f32"),
+             (workloads.duct(33, 91, 20, (0.02, 0.01, 0.01), 0.8), "f32"),
+             (workloads.duct(127, 98, 100, (0.04, 0.01, 0.01), 0.8), "f64"),
+             (workloads.duct(128, 97, 113, (0.02, -0.01, 0.01), 1.1), "f64"),
+             (workloads.duct(64, 20, 20, (0.03, 0.0, 0.01), 0.9), "f16sr")]
+    got = []
+    for one_step in (False, True):
+        b = lbm.lbm_batch_create(4 << 30, chunk, 8)
+        try:
+            if one_step:
+                lbm.lbm_batch_set_steps_per_pass(b, 1, 0)
+            lbm.lbm_batch_set_shape(b, *shape)
+            ids = [lbm.lbm_batch_submit(b, serving.job_for(s, st, 0.0, 2 * chunk)) for s, st in items]
+            while lbm.lbm_batch_run_chunk(b) != (0, 0):
+                pass
+            # one captured chunk: the passes of two storage forms
+            assert _passes(b) == (0 if one_step else 2 * (((chunk - 1) // 2) & ~1))
+            got.append([(lbm.lbm_batch_poll(b, i).delta, *lbm.lbm_batch_result(b, i, s.nodes))
+                        for i, (s, _) in zip(ids, items)])
+        finally:
+            lbm.lbm_batch_destroy(b)
+    for (s, st), x, y in zip(items, *got):
+        assert x[0] == y[0] and (x[1] == y[1]).all() and (x[2] == y[2]).all(), (s.name, st)
