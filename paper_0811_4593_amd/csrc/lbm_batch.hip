@@ -884,7 +884,7 @@ bool padding_pays(const lbm_batch *B, const Job &J, bool shared, bool passes) {
   c.ny = J.spec.ny;
   c.nz = J.spec.nz;
   c.layout = layout_of(LBM_LAYOUT_ROW_MAJOR, J.nodes, c.nx, lbm_element_bytes(J.spec.storage));
-  return lbm::block_steps(c) > 0 || lbm::sweep2_pays(c, B->num_cu) > 0;
+  return lbm::block_steps(c, B->num_cu) > 0 || lbm::sweep2_pays(c, B->num_cu) > 0;
 }
 void drop_padding(Job &J) {
   if (unpadded_bytes(J) == J.bytes) return;
@@ -1088,7 +1088,7 @@ lbm_status run_solo_chunk(lbm_batch *B, Lane &ln, int slot) {
     launches = passes_in(B->chunk_steps);
     zc = B->pass_zc;
   } else if (B->pass_auto) {
-    per = lbm::block_steps(c);
+    per = lbm::block_steps(c, B->num_cu);
     if (per == 0) {
       zc = lbm::sweep2_pays(c, B->num_cu);
       per = zc > 0 ? 2 : 0;
@@ -1100,7 +1100,8 @@ lbm_status run_solo_chunk(lbm_batch *B, Lane &ln, int slot) {
     c.step = unsigned(J.steps + per * i);
     const void *from = L.buf[i & 1];
     void *to = L.buf[(i & 1) ^ 1];
-    LBM_BHIP(zc > 0 ? lbm::launch_sweep2(c, zc, 0, from, to, ln.stream) : lbm::launch_block_steps(c, from, to, ln.stream),
+    LBM_BHIP(zc > 0 ? lbm::launch_sweep2(c, zc, 0, from, to, ln.stream)
+                    : lbm::launch_block_steps(c, per, from, to, ln.stream),
              "launch of several steps");
   }
   for (int s = per * launches; s < B->chunk_steps; ++s) {

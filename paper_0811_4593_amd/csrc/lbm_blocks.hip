@@ -6,8 +6,8 @@
 // STEPS steps of it without any exchange with the others: step t is computed
 // on the block and STEPS - t nodes around it, the first from HBM (through L2),
 // the later ones from LDS, and only the last is written back.  The nodes
-// around the blocks are computed by several workgroups, two to four times the
-// updates in all, on compute units that would stand idle.  The arithmetic of
+// around the blocks are computed by several workgroups, 1.8 (bars) to 4.1
+// (cubes) times the updates in all, on compute units that would stand idle.  The arithmetic of
 // every node is the single sweep's, so the state is the same bit for bit.
 #include <hip/hip_runtime.h>
 
@@ -39,8 +39,9 @@ struct Block {
     return (BX + 2 * (STEPS - t)) * (BY + 2 * (STEPS - t)) * (BZ + 2 * (STEPS - t));
   }
   static constexpr int kThreads = cells(1) <= 1024 ? (cells(1) + 63) / 64 * 64 : 1024;
-  // LDS elements: the populations of step 1's cells and, for three steps or
-  // more, of step 2's; later steps write over the older of the two.
+  // LDS elements: the populations of step 1's cells and, for three steps, of
+  // step 2's.
+  static_assert(STEPS == 2 || STEPS == 3, "the steps block_steps_kernel makes");
   static constexpr int kElements = 19 * (cells(1) + (STEPS > 2 ? cells(2) : 0));
 };
 
@@ -125,13 +126,9 @@ __global__ __launch_bounds__(B::kThreads) void block_steps_kernel(const typename
   block_step<F, B, 1>(src, dst, a, ox, oy, oz, nullptr, one);
   __syncthreads();
   block_step<F, B, 2>(src, dst, a, ox, oy, oz, one, two);
-  if constexpr (B::kSteps >= 3) {
+  if constexpr (B::kSteps == 3) {
     __syncthreads();
-    block_step<F, B, 3>(src, dst, a, ox, oy, oz, two, one);
-  }
-  if constexpr (B::kSteps >= 4) {
-    __syncthreads();
-    block_step<F, B, 4>(src, dst, a, ox, oy, oz, one, two);
+    block_step<F, B, 3>(src, dst, a, ox, oy, oz, two, nullptr);
   }
 }
 
@@ -172,25 +169,23 @@ size_t blocks_of(const SweepConfig &c) {
          size_t((c.nz + B::kBZ - 1) / B::kBZ);
 }
 
-constexpr size_t kMostBlocks = 256;  // one workgroup per compute unit
-
 }  // namespace
 
 // Cubes of three steps while there is a compute unit for each (up to about
-// 16000 nodes), then bars of two steps (up to about 65000): measured per
-// step, single sweeps and so: 16 x 16 x 32 FP64 4.9 / 3.1 us, FP32 5.3 / 2.7;
+// 16000 nodes with 256 units), then bars of two steps (up to about 65000):
+// measured per step, single sweeps and so: 16 x 16 x 32 FP64 4.9 / 3.1 us, FP32 5.3 / 2.7;
 // 16^3 FP32 duct 5.7 / 3.4; 32^3 FP32 5.9 / 4.7; 64 x 32 x 32 FP32 5.9 / 5.6.
 // A second round of workgroups costs more than it saves (cubes on 32^3: 5.5
 // us, on 64 x 32 x 32: 8.5).
-int block_steps(const SweepConfig &c) {
+int block_steps(const SweepConfig &c, int compute_units) {
   if (c.nx < 3 || c.ny < 3 || c.nz < 3) return 0;  // wrapped() goes once around
-  if (blocks_of<Cube>(c) <= kMostBlocks) return Cube::kSteps;
-  if (blocks_of<Bar>(c) <= kMostBlocks) return Bar::kSteps;
+  if (blocks_of<Cube>(c) <= size_t(compute_units)) return Cube::kSteps;
+  if (blocks_of<Bar>(c) <= size_t(compute_units)) return Bar::kSteps;
   return 0;
 }
 
-hipError_t launch_block_steps(const SweepConfig &c, const void *src, void *dst, hipStream_t s) {
-  const int steps = block_steps(c);
+hipError_t launch_block_steps(const SweepConfig &c, int steps, const void *src, void *dst, hipStream_t s) {
+  if (c.nx < 3 || c.ny < 3 || c.nz < 3) return hipErrorInvalidValue;
 #define LBM_CASE(ST, F)                                                \
   case ST:                                                             \
     if (steps == Cube::kSteps) return launch_t<F, Cube>(c, src, dst, s); \

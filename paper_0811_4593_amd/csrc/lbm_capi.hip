@@ -499,7 +499,7 @@ static StepPlan step_plan(const lbm_lattice *L, const lbm::SweepConfig &c, int n
     if (lbm::sweep2_takes(L->lay, L->ny, L->storage)) p = {2, nsteps / 2, L->zc, L->tile_rows};
     return p;
   }
-  const int block = L->blocks ? lbm::block_steps(c) : 0;
+  const int block = L->blocks ? lbm::block_steps(c, L->compute_units) : 0;
   if (block > 0) {
     p = {block, nsteps / block, 0, 0};
   } else if (L->pass_auto && nsteps >= 4) {
@@ -536,7 +536,7 @@ lbm_status lbm_step(lbm_lattice *L, int nsteps) {
     void *to = L->buf[L->cur ^ 1];
     const hipError_t e = n == 1     ? lbm::launch_sweep(c, from, to, false, L->stream)
                          : p.zc > 0 ? lbm::launch_sweep2(c, p.zc, p.tile_rows, from, to, L->stream)
-                                    : lbm::launch_block_steps(c, from, to, L->stream);
+                                    : lbm::launch_block_steps(c, p.group, from, to, L->stream);
     if (e != hipSuccess) return hip_fail(e, n == 1 ? "sweep launch" : "launch of several steps");
     L->cur ^= 1;
     L->steps += unsigned(n);
@@ -768,7 +768,7 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
       for (int zc : zcs)
         for (int xcd : {LBM_XCD_SLABS, LBM_XCD_NONE}) cands.push_back({2, L->block_x, L->npt, xcd, zc, rows});
     }
-  const int block = ext ? 0 : lbm::block_steps(sweep_config(L));
+  const int block = ext ? 0 : lbm::block_steps(sweep_config(L), L->compute_units);
   if (block > 0) cands.push_back({0, L->block_x, L->npt, L->xcd, 0, 0});
   const bool old_auto = L->pass_auto, old_blocks = L->blocks;
   L->pass_auto = L->blocks = false;
@@ -800,7 +800,7 @@ lbm_status lbm_autotune(lbm_lattice *L, int trial_steps, int *block_x, int *node
     auto take = [&](int steps, int blocks) {
       const lbm::SweepConfig sc = sweep_config(L);
       for (int b = 0; b < blocks; ++b) {
-        const hipError_t e = lbm::launch_block_steps(sc, L->buf[L->cur], L->buf[L->cur ^ 1], L->stream);
+        const hipError_t e = lbm::launch_block_steps(sc, block, L->buf[L->cur], L->buf[L->cur ^ 1], L->stream);
         if (e != hipSuccess) return hip_fail(e, "launch of several steps");
       }
       return blocks > 0 ? LBM_OK : lbm_step(L, steps);

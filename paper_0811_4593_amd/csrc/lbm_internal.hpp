@@ -104,15 +104,15 @@ hipError_t launch_sweep(const SweepConfig &c, const void *src, void *dst, bool c
 hipError_t launch_sweep_delta(const SweepConfig &c, const void *src, void *dst, float *snap, double inv_uref,
                               float *partials, unsigned *delta_bits, hipStream_t s);
 size_t sweep_delta_partials(const SweepConfig &c);
-// Two steps (c.step and c.step + 1) in one pass, row-major layout, no solid
-// mask, face field or geometry; z ranges of zc planes per workgroup; tiles of
-// `rows` interior rows (5, or 0 for the form's default).
-// Whether the pass takes a lattice: row-major (the tile's rows are whole rows
+// Whether the two-step pass takes a lattice: row-major (the tile's rows are whole rows
 // of one population), a z plane's bytes within the 32-bit offsets of a buffer
 // descriptor.
 bool sweep2_takes(const PopLayout &lay, int ny, int storage);
 // Interior rows of the pass's tiles for a storage form and tile_rows (0, 5 or 12).
 int sweep2_rows(int storage, int tile_rows);
+// Two steps (c.step and c.step + 1) in one pass, on a lattice it takes without
+// solid mask, face field or geometry; z ranges of zc planes per workgroup;
+// tiles of `rows` interior rows (5, 12, or 0 for the form's default).
 hipError_t launch_sweep2(const SweepConfig &c, int zc, int rows, const void *src, void *dst, hipStream_t s);
 
 // The z range (planes per workgroup) a pass takes least time with, estimated,
@@ -128,11 +128,11 @@ int sweep2_pays(const SweepConfig &c, int compute_units);
 // Compute units of the current device (256 if it cannot be asked).
 int device_compute_units();
 
-// Steps one launch_block_steps launch makes on a lattice without solid mask,
-// face field or geometry (c.step and the following), or 0 where single sweeps
-// are faster.
-int block_steps(const SweepConfig &c);
-hipError_t launch_block_steps(const SweepConfig &c, const void *src, void *dst, hipStream_t s);
+// Steps (c.step and the following) that a launch by blocks makes on a lattice
+// without solid mask, face field or geometry, or 0 where single sweeps are
+// faster; and that launch.
+int block_steps(const SweepConfig &c, int compute_units);
+hipError_t launch_block_steps(const SweepConfig &c, int steps, const void *src, void *dst, hipStream_t s);
 
 // Node codes of a complex geometry from node types (0 fluid, 1 wall node,
 // 2 solid interior), all axes periodic; code[n] as geo_code().  Returns the
