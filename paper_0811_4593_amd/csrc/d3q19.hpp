@@ -75,7 +75,11 @@ __device__ __forceinline__ float fused_add(float a, float b, float c) { return _
 // a / den with inv = 1 / den rounded to nearest: the quotient a * inv
 // corrected once by its exact remainder is the rounded quotient (Markstein,
 // IBM J. Res. Dev. 34(1), 1990), in three operations where the division takes
-// about twelve, one after the other.
+// about twelve, one after the other.  For finite a: of an infinite one it makes
+// NaN where the division gives infinity.  No state shows that: a is infinite
+// only where a population of the node is, then its density is too, and the
+// collision makes NaN of every population of the node (1.5 rho u^2 = infinity
+// times 0, or NaN) either way.
 template <class T>
 __device__ __forceinline__ T quotient(T a, T den, T inv) {
   const T q = a * inv;
