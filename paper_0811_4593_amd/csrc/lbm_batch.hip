@@ -913,6 +913,9 @@ lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) 
   const bool pass2 = B->pass_steps == 2;
   if (jobs != ln.table_jobs || ln.table_tile_nodes != B->shape.tile_nodes || ln.table_pass != (B->pass_auto ? 0 : B->pass_steps) ||
       ln.table_zc != B->pass_zc) {
+    // Until they are written as a whole the tables describe no jobs: a call that
+    // fails half way (an allocation) leaves them to be rebuilt by the next.
+    ln.table_tile_nodes = 0;
     std::vector<lbm::BatchTile> tiles[kNumStorage];
     std::vector<lbm::BatchBox> boxes[kNumStorage];
     const unsigned tn = unsigned(B->shape.tile_nodes);
