@@ -599,6 +599,9 @@ struct Tuned {
   int zc = 32, remap = 1;
 };
 
+// What a chunk's launches are, most of them.
+enum class Kind { kSingles, kBlocks, kPasses };
+
 // Autotune results shared by every batch in the process, keyed by a coarse
 // description of the resident work (storage mix, log2 of the node count,
 // steps per pass); batches on different threads share it under a lock.
@@ -616,6 +619,7 @@ struct Lane {
   hipEvent_t done = nullptr;
   bool busy = false;
   std::vector<int> slots;  // slots the chunk in flight steps
+  Kind wanted = Kind::kSingles;  // what its jobs would make with the device to themselves
   lbm::BatchLat *d_lats = nullptr;
   unsigned *d_delta = nullptr;
   int *d_ntiles = nullptr;  // per storage form: tile counts, box counts, tiles of the jobs without boxes
@@ -869,22 +873,29 @@ size_t unpadded_bytes(const Job &J) {
   return std::min(J.bytes, job_bytes(J.spec, batch_layout_kind(J.spec.nx, lbm_element_bytes(J.spec.storage))));
 }
 
-// Whether a queued job padded for passes is worth the padding.  shared: there
-// are more jobs than lanes, and those of its form make passes in their chunks;
-// otherwise every job has a lane to itself, and the job's own kernels have to
-// group its steps (run_solo_chunk).  Without either, padded rows only cost:
-// four 50 x 78 x 80 FP32 ducts, too few boxes for passes, take 40 us per step
-// unpadded and 49 padded; one of 100^3 33 and 37; four of 100^3 on a lane
-// each 116 and 143.
-bool padding_pays(const lbm_batch *B, const Job &J, bool shared, bool passes) {
-  if (shared) return passes;
+// Launches that a row-major job makes in a chunk of its own, with the device
+// to itself and no steps per pass asked for.
+Kind solo_kind(const lbm_batch *B, const lbm_job &j) {
   lbm::SweepConfig c{};
-  c.storage = J.spec.storage;
-  c.nx = J.spec.nx;
-  c.ny = J.spec.ny;
-  c.nz = J.spec.nz;
-  c.layout = layout_of(LBM_LAYOUT_ROW_MAJOR, J.nodes, c.nx, lbm_element_bytes(J.spec.storage));
-  return lbm::block_steps(c, B->num_cu) > 0 || lbm::sweep2_pays(c, B->num_cu) > 0;
+  c.storage = j.storage;
+  c.nx = j.nx;
+  c.ny = j.ny;
+  c.nz = j.nz;
+  c.layout = layout_of(LBM_LAYOUT_ROW_MAJOR, size_t(j.nx) * j.ny * j.nz, j.nx, lbm_element_bytes(j.storage));
+  if (lbm::block_steps(c, B->num_cu) > 0) return Kind::kBlocks;
+  return lbm::sweep2_pays(c, B->num_cu) > 0 ? Kind::kPasses : Kind::kSingles;
+}
+
+// Whether launches of several steps may run beside those of other lanes: only
+// where all lanes' jobs would make the same kind.  A workgroup of a pass holds
+// a compute unit for its whole z range, and one of a pass or a block needs
+// most of a compute unit free at once.  Beside a large job's passes every
+// launch of a small job waits for a unit (60^3 FP32 beside 256^3 FP32: 58 us
+// per step, 19 beside single sweeps); beside a large job's single sweeps, whose
+// small workgroups take up whatever another frees, blocks starve (32^3 FP32
+// beside 256^3 FP16: 96 us per step by blocks, 11 by single sweeps).
+bool same_kinds(const std::vector<Kind> &k) {
+  return std::all_of(k.begin(), k.end(), [&](Kind x) { return x == k[0]; });
 }
 void drop_padding(Job &J) {
   if (unpadded_bytes(J) == J.bytes) return;
@@ -903,15 +914,28 @@ unsigned present_mask(const Lane &ln) {
   return m;
 }
 
+// The jobs in `slots` whose storage form makes passes in a shared chunk without
+// being asked to, by form.
+void passes_of(const lbm_batch *B, const std::vector<int> &slots, bool (&pays)[kNumStorage]) {
+  PassLoad load[kNumStorage];
+  for (int slot : slots) {
+    const Job &J = B->jobs.at(B->slot_job[slot]);
+    if (J.passes && B->pass_auto) load[J.spec.storage].add(J.spec);
+  }
+  for (int st = 0; st < kNumStorage; ++st) pays[st] = chunk_passes_pay(load[st], st, B->num_cu, B->lanes.size());
+}
+
 // Tables of a lane for the jobs in `slots`: the descriptors (with the step
-// counts as step_base) always, the tile lists when the job set or the tile
-// size changed.  Asynchronous copies from page-locked staging on the lane's
+// counts as step_base) always, the tile lists when the job set, the tile size
+// or the passes changed.  passes: with one step per pass, whether the jobs for
+// which they pay make them.  Asynchronous copies from page-locked staging on the lane's
 // stream; the lane is idle.
-lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) {
+lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots, bool passes) {
   std::vector<std::pair<int, int>> jobs;
   for (int slot : slots) jobs.push_back({slot, B->slot_job[slot]});
   const bool pass2 = B->pass_steps == 2;
-  if (jobs != ln.table_jobs || ln.table_tile_nodes != B->shape.tile_nodes || ln.table_pass != (B->pass_auto ? 0 : B->pass_steps) ||
+  const int mode = B->pass_auto && passes ? 0 : B->pass_steps;
+  if (jobs != ln.table_jobs || ln.table_tile_nodes != B->shape.tile_nodes || ln.table_pass != mode ||
       ln.table_zc != B->pass_zc) {
     // Until they are written as a whole the tables describe no jobs: a call that
     // fails half way (an allocation) leaves them to be rebuilt by the next.
@@ -922,14 +946,9 @@ lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) 
     const int zc = pass_planes(B);
     // Jobs that take passes: all with two steps per pass; otherwise those of
     // a storage form for which they pay together.
-    PassLoad load[kNumStorage];
-    bool pays[kNumStorage];
-    for (int slot : slots) {
-      const Job &J = B->jobs.at(B->slot_job[slot]);
-      if (J.passes && B->pass_auto) load[J.spec.storage].add(J.spec);
-    }
-    for (int st = 0; st < kNumStorage; ++st) pays[st] = chunk_passes_pay(load[st], st, B->num_cu, B->lanes.size());
-    auto takes_passes = [&](const Job &J) { return pass2 || (J.passes && B->pass_auto && pays[J.spec.storage]); };
+    bool pays[kNumStorage] = {false, false, false, false};
+    if (mode == 0) passes_of(B, slots, pays);
+    auto takes_passes = [&](const Job &J) { return pass2 || (J.passes && pays[J.spec.storage]); };
     for (int with_boxes = 0; with_boxes < 2; ++with_boxes) {
       for (int slot : slots) {
         const Job &J = B->jobs.at(B->slot_job[slot]);
@@ -984,7 +1003,7 @@ lbm_status upload_tables(lbm_batch *B, Lane &ln, const std::vector<int> &slots) 
     if (st != LBM_OK) return st;
     ln.table_jobs = jobs;
     ln.table_tile_nodes = B->shape.tile_nodes;
-    ln.table_pass = B->pass_auto ? 0 : B->pass_steps;
+    ln.table_pass = mode;
     ln.table_zc = B->pass_zc;
   }
   lbm::BatchLat *h = ln.h_lats.as<lbm::BatchLat>();
@@ -1075,13 +1094,13 @@ bool measured_in_last_step(const lbm_batch *B, bool solo) {
 // A chunk that steps a single job: plain launches of the single-lattice
 // kernels on the job's buffers (row-aligned blocks; bitwise the batch sweep's
 // results), each with the job's own step index.  First launches of several
-// steps: passes with two steps per pass set; otherwise, unless one step per
-// pass was asked for, as lbm_step does -- blocks of steps for a small job,
-// passes for a larger one where they pay.  Then single steps, of which the
+// steps: passes with two steps per pass set; otherwise (grouped), unless one
+// step per pass was asked for, as lbm_step does -- blocks of steps for a small
+// job, passes for a larger one where they pay.  Then single steps, of which the
 // last also takes the convergence measure.  Launches of two steps come in
 // pairs, so that the chunk ends in buf[0] (launches of three do not change
 // the parity).
-lbm_status run_solo_chunk(lbm_batch *B, Lane &ln, int slot) {
+lbm_status run_solo_chunk(lbm_batch *B, Lane &ln, int slot, bool grouped) {
   const Job &J = B->jobs.at(B->slot_job[slot]);
   const lbm::BatchLat &L = B->lat[slot];
   lbm::SweepConfig c = J.cfg;
@@ -1090,7 +1109,7 @@ lbm_status run_solo_chunk(lbm_batch *B, Lane &ln, int slot) {
     per = 2;
     launches = passes_in(B->chunk_steps);
     zc = B->pass_zc;
-  } else if (B->pass_auto) {
+  } else if (B->pass_auto && grouped) {
     per = lbm::block_steps(c, B->num_cu);
     if (per == 0) {
       zc = lbm::sweep2_pays(c, B->num_cu);
@@ -1212,8 +1231,15 @@ lbm_status admit(lbm_batch *B) {
     for (int id : B->slot_job)
       if (id >= 0) jobs.push_back(&B->jobs.at(id));
     for (int id : B->queue) jobs.push_back(&B->jobs.at(id));
+    // The padding is worth it where there are more jobs than lanes, so that
+    // chunks are shared, and those of the job's form make passes in them, or
+    // where every job has a lane to itself and all group their steps alike.
+    // Elsewhere padded rows only cost: four 50 x 78 x 80 FP32 ducts, too few
+    // boxes for passes, take 40 us per step unpadded and 49 padded; one of
+    // 100^3 33 and 37; four of 100^3 on a lane each 116 and 143.
     const bool shared = jobs.size() > B->lanes.size();
     int passes[kNumStorage] = {-1, -1, -1, -1};  // not asked, no, yes
+    int alike = -1;
     for (int id : B->queue) {
       Job &J = B->jobs.at(id);
       if (!J.for_passes) continue;
@@ -1224,7 +1250,13 @@ lbm_status admit(lbm_batch *B) {
           if (o->passes && o->spec.storage == J.spec.storage) load.add(o->spec);
         p = chunk_passes_pay(load, J.spec.storage, B->num_cu, 1);
       }
-      if (!padding_pays(B, J, shared, p > 0)) drop_padding(J);
+      if (!shared && alike < 0) {
+        std::vector<Kind> kinds;
+        for (const Job *o : jobs)
+          kinds.push_back(o->layout == LBM_LAYOUT_ROW_MAJOR ? solo_kind(B, o->spec) : Kind::kSingles);
+        alike = kinds[0] != Kind::kSingles && same_kinds(kinds);
+      }
+      if (shared ? p <= 0 : alike == 0) drop_padding(J);
     }
   }
   size_t need = 0, slack = B->pool.capacity() - B->pool.used();
@@ -1434,9 +1466,25 @@ std::vector<std::pair<int, std::vector<int>>> plan_chunks(lbm_batch *B) {
   return plan;
 }
 
+// One row-major job alone: the single-lattice sweep (population-major rows that
+// are not whole lines run faster in the batch's flat walk).
+bool runs_solo(const lbm_batch *B, const std::vector<int> &slots) {
+  return slots.size() == 1 && B->jobs.at(B->slot_job[slots[0]]).layout == LBM_LAYOUT_ROW_MAJOR;
+}
+
+// What a chunk of these jobs makes with the device to itself.
+Kind wanted_kind(const lbm_batch *B, const std::vector<int> &slots) {
+  if (!B->pass_auto) return Kind::kSingles;
+  if (runs_solo(B, slots)) return solo_kind(B, B->jobs.at(B->slot_job[slots[0]]).spec);
+  bool pays[kNumStorage];
+  passes_of(B, slots, pays);
+  return std::any_of(pays, pays + kNumStorage, [](bool p) { return p; }) ? Kind::kPasses : Kind::kSingles;
+}
+
 // Enqueue one chunk of the jobs in `slots` on a lane: the steps, then the
 // convergence measure and its copy to the host, then the lane's event.
-lbm_status start_chunk(lbm_batch *B, int l, const std::vector<int> &slots) {
+// grouped: launches of several steps where they pay and are not asked for.
+lbm_status start_chunk(lbm_batch *B, int l, const std::vector<int> &slots, bool grouped) {
   Lane &ln = B->lanes[l];
   int running = 0;
   for (size_t o = 0; o < B->lanes.size(); ++o) {
@@ -1448,11 +1496,9 @@ lbm_status start_chunk(lbm_batch *B, int l, const std::vector<int> &slots) {
       return bfail(LBM_ERR_HIP, "event query: %s", hipGetErrorString(q));
   }
   if (B->init_recorded) LBM_BHIP(hipStreamWaitEvent(ln.stream, B->init_done, 0), "wait for initialisation");
-  lbm_status st = upload_tables(B, ln, slots);
+  lbm_status st = upload_tables(B, ln, slots, grouped);
   if (st != LBM_OK) return st;
-  // one row-major job alone: the single-lattice sweep (population-major
-  // rows that are not whole lines run faster in the batch's flat walk)
-  const bool solo = slots.size() == 1 && B->jobs.at(B->slot_job[slots[0]]).layout == LBM_LAYOUT_ROW_MAJOR;
+  const bool solo = runs_solo(B, slots);
   // The convergence maxima start at zero (a fill kernel rather than a
   // memset: they are the bit patterns of non-negative floats, and 0.0f is
   // all zero bits); the chunk's last step takes the measure, or, when the
@@ -1461,7 +1507,7 @@ lbm_status start_chunk(lbm_batch *B, int l, const std::vector<int> &slots) {
   lbm::fill_float_kernel<<<dim3(unsigned((nd + 255) / 256)), dim3(256), 0, ln.stream>>>(
       reinterpret_cast<float *>(ln.d_delta), nd, 0.0f);
   LBM_BHIP(hipGetLastError(), "reset deltas");
-  st = solo ? run_solo_chunk(B, ln, slots[0]) : run_graph_chunk(B, ln);
+  st = solo ? run_solo_chunk(B, ln, slots[0], grouped) : run_graph_chunk(B, ln);
   if (st != LBM_OK) return st;
   // the measure: combined from the last step's per-wave maxima, or (after
   // a pass, or with persistent workgroups) taken from the state; persistent
@@ -1747,8 +1793,15 @@ lbm_status lbm_batch_run_chunk(lbm_batch *B, int *n_active, int *n_queued) {
   if (!B) return bfail(LBM_ERR_ARG, "NULL handle");
   lbm_status st = admit(B);
   if (st != LBM_OK) return st;
-  for (const auto &p : plan_chunks(B)) {
-    st = start_chunk(B, p.first, p.second);
+  // The chunks to start beside those in flight group their steps only if the
+  // jobs of all of them would do so alike.
+  const auto plan = plan_chunks(B);
+  std::vector<Kind> kinds;
+  for (const auto &p : plan) kinds.push_back(B->lanes[p.first].wanted = wanted_kind(B, p.second));
+  for (const Lane &ln : B->lanes)
+    if (ln.busy) kinds.push_back(ln.wanted);
+  for (const auto &p : plan) {
+    st = start_chunk(B, p.first, p.second, same_kinds(kinds));
     if (st != LBM_OK) return st;
   }
   st = wait_and_finish(B);
@@ -1858,7 +1911,7 @@ lbm_status lbm_batch_autotune(lbm_batch *B, int trial_steps, int *block_x, int *
   std::vector<int> all;
   for (int slot = 0; slot < B->max_jobs; ++slot)
     if (B->slot_job[slot] >= 0) all.push_back(slot);
-  st = upload_tables(B, ln, all);
+  st = upload_tables(B, ln, all, true);
   if (st != LBM_OK) return st;
   const long long key = tune_key(B, ln);
   Tuned cached;
@@ -1912,7 +1965,7 @@ lbm_status lbm_batch_autotune(lbm_batch *B, int trial_steps, int *block_x, int *
       st = lbm_batch_set_shape(B, c.shape.block_x, c.shape.tile_nodes, c.shape.grid);
       B->pass_zc = c.zc;
       B->pass_remap = c.remap;
-      if (st == LBM_OK) st = upload_tables(B, ln, all);
+      if (st == LBM_OK) st = upload_tables(B, ln, all, true);
       hipError_t e = hipSuccess;
       auto each_form = [&](auto launch) {
         for (int s = 0; s < kNumStorage && st == LBM_OK; ++s)
