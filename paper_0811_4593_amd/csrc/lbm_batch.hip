@@ -661,7 +661,9 @@ struct lbm_batch {
   // workgroup, box order pass_remap on the XCDs.
   int pass_steps = 1, pass_zc = 32, pass_remap = 1;
   bool pass_auto = true;  // lbm_batch_set_steps_per_pass has not been called
-  long long pass_launches = 0;  // multi-lattice passes enqueued (those of a captured chunk once)
+  // Launches of several steps enqueued: multi-lattice passes (those of a
+  // captured chunk once), and those of chunks of one job.
+  long long pass_launches = 0, solo_grouped = 0;
   std::map<int, Job> jobs;
   std::deque<int> queue;
   std::vector<int> slot_job;           // slot -> job id (-1 free)
@@ -1126,6 +1128,7 @@ lbm_status run_solo_chunk(lbm_batch *B, Lane &ln, int slot, bool grouped) {
                     : lbm::launch_block_steps(c, per, from, to, ln.stream),
              "launch of several steps");
   }
+  B->solo_grouped += launches;
   for (int s = per * launches; s < B->chunk_steps; ++s) {
     const int q = (s - per * launches + launches) & 1;
     c.step = unsigned(J.steps + s);
@@ -2033,11 +2036,11 @@ lbm_status lbm_batch_get_stats(const lbm_batch *B, lbm_batch_stats *stats) {
   return LBM_OK;
 }
 
-// For the tests: passes of two steps enqueued by the batch's multi-lattice
-// kernel so far (a captured chunk's count once), and the box order of the next.
-void lbm_internal_batch_passes(const lbm_batch *B, long long *launches, int *box_order) {
-  *launches = B->pass_launches;
-  *box_order = B->pass_remap;
+// For the tests: launches of several steps enqueued so far, those of the
+// multi-lattice pass (a captured chunk's once) and of chunks of one job.
+void lbm_internal_batch_launches(const lbm_batch *B, long long *passes, long long *solo) {
+  *passes = B->pass_launches;
+  *solo = B->solo_grouped;
 }
 
 }  // extern "C"

@@ -95,10 +95,15 @@ def test_padding_only_where_steps_are_grouped(jobs, padded, lanes):
     assert _padded(jobs, 100, lanes) == padded
 
 
+def _launches(b):
+    """Launches of several steps so far: multi-lattice passes, and those of chunks of one job."""
+    out = ctypes.c_longlong(), ctypes.c_longlong()
+    ctypes.CDLL(lbm.LIB_PATH).lbm_internal_batch_launches(ctypes.c_void_p(b), *map(ctypes.byref, out))
+    return tuple(v.value for v in out)
+
+
 def _passes(b):
-    launches, order = ctypes.c_longlong(), ctypes.c_int()
-    ctypes.CDLL(lbm.LIB_PATH).lbm_internal_batch_passes(ctypes.c_void_p(b), ctypes.byref(launches), ctypes.byref(order))
-    return launches.value
+    return _launches(b)[0]
 
 
 # (each mix of forms is tuned once in a process)
@@ -161,3 +166,48 @@ def test_shared_chunks_by_passes(chunk, shape):
             lbm.lbm_batch_destroy(b)
     for (s, st), x, y in zip(items, *got):
         assert x[0] == y[0] and (x[1] == y[1]).all() and (x[2] == y[2]).all(), (s.name, st)
+
+
+LARGE, SMALL = workloads.duct(128, 96, 96, (0.03, 0.01, 0.0), 0.9), workloads.duct(30, 30, 30, (0.02, 0.01, 0.0), 0.9)
+
+
+def _grouped(policy, jobs, rounds=1):
+    """Launches of several steps that chunks of one job make in `rounds` rounds
+    of a batch with four lanes, and the fields of the jobs at their end."""
+    b = lbm.lbm_batch_create(1 << 30, 20, 8)
+    try:
+        lbm.lbm_batch_set_policy(b, policy, 1 << 18)
+        lbm.lbm_batch_set_lanes(b, 4)
+        ids = [lbm.lbm_batch_submit(b, serving.job_for(s, st, 0.0, n)) for s, st, n in jobs]
+        for _ in range(rounds):
+            lbm.lbm_batch_run_chunk(b)
+        n = _launches(b)[1]
+        while lbm.lbm_batch_run_chunk(b) != (0, 0):
+            pass
+        return n, _launches(b)[1], [lbm.lbm_batch_result(b, i, s.nodes) for i, (s, _, _) in zip(ids, jobs)]
+    finally:
+        lbm.lbm_batch_destroy(b)
+
+
+def test_lanes_group_steps_only_alike():
+    """Alone, a job groups its steps (20: 8 passes or 8 blocks of two); beside a job
+    whose launches are of another kind it does not, in whichever order they
+    come; beside one of its own kind it does; the bits are the same."""
+    order = lbm.LBM_BATCH_LARGE_IN_ORDER
+    n, _, alone = _grouped(order, [(LARGE, "f64", 20)])
+    assert n == 8
+    n, _, small = _grouped(order, [(SMALL, "f32", 20)])
+    assert n == 8
+    for jobs in ([(LARGE, "f64", 20), (SMALL, "f32", 20)], [(SMALL, "f32", 20), (LARGE, "f64", 20)]):
+        n, _, both = _grouped(order, jobs)
+        assert n == 0
+        for (s, _, _), (rho, u) in zip(jobs, both):
+            r, v = (alone if s is LARGE else small)[0]
+            assert (rho == r).all() and (u == v).all()
+    # FP16 makes single sweeps at this size: a small job beside it does not make blocks
+    assert _grouped(order, [(LARGE, "f16sr", 20), (SMALL, "f32", 20)])[0] == 0
+    assert _grouped(order, [(SMALL, "f32", 20), (SMALL, "f64", 20)])[0] == 16
+    assert _grouped(lbm.LBM_BATCH_SHORTEST_FIRST, [(LARGE, "f64", 20), (LARGE, "f32", 20)])[0] == 16
+    # the large job goes back to passes when the small one has ended
+    n, total, _ = _grouped(order, [(LARGE, "f64", 200), (SMALL, "f32", 20)])
+    assert n == 0 and total >= 8 * 7
