@@ -187,9 +187,12 @@ __device__ __forceinline__ void face_values(unsigned m, const NodeParams<T> &p, 
 // nodes are the ones the others of a workgroup wait for, so what counts is
 // the length of the rules' dependent chains: in the two-step pass a plane of
 // a workgroup at the faces took 7.4 us, 4.5 us with no rules at all.  This
-// form against divergent branches and divisions: 256 x 128 x 128 FP32 0.110
-// -> 0.100 ms per step, 64 x 64 x 65 FP64 17.1 -> 15.6 us, 512 x 256 x 256
-// FP16 0.494 -> 0.458 ms.
+// form against divergent branches and divisions, two steps per pass: 256 x 128
+// x 128 FP32 0.110 -> 0.100 ms per step, 512 x 256 x 256 FP16 0.494 -> 0.458
+// ms.  In the single sweep of rows of up to 64 nodes, where every wave holds
+// both x faces and runs both rules, it is from 15% faster (64 x 64 x 65 FP16
+// 7.7 -> 6.7 us per step) to 3% slower (48 x 100 x 100 FP32 19.6 -> 20.2);
+// divergent branches around these rules there are slower still (21.3).
 
 // Values of one face.
 template <class T>

@@ -619,7 +619,11 @@ struct Lane {
   hipEvent_t done = nullptr;
   bool busy = false;
   std::vector<int> slots;  // slots the chunk in flight steps
-  Kind wanted = Kind::kSingles;  // what its jobs would make with the device to themselves
+  // What these jobs (slot, job id) would make with the device to themselves,
+  // one of so many lanes.
+  Kind wanted = Kind::kSingles;
+  std::vector<std::pair<int, int>> wanted_jobs;
+  size_t wanted_lanes = 0;
   lbm::BatchLat *d_lats = nullptr;
   unsigned *d_delta = nullptr;
   int *d_ntiles = nullptr;  // per storage form: tile counts, box counts, tiles of the jobs without boxes
@@ -1475,13 +1479,22 @@ bool runs_solo(const lbm_batch *B, const std::vector<int> &slots) {
   return slots.size() == 1 && B->jobs.at(B->slot_job[slots[0]]).layout == LBM_LAYOUT_ROW_MAJOR;
 }
 
-// What a chunk of these jobs makes with the device to itself.
-Kind wanted_kind(const lbm_batch *B, const std::vector<int> &slots) {
-  if (!B->pass_auto) return Kind::kSingles;
-  if (runs_solo(B, slots)) return solo_kind(B, B->jobs.at(B->slot_job[slots[0]]).spec);
+// What a chunk of these jobs makes with the device to itself (kept with the
+// lane: a box list takes up to a millisecond to play).
+Kind wanted_kind(const lbm_batch *B, Lane &ln, const std::vector<int> &slots) {
+  if (!B->pass_auto || runs_solo(B, slots)) {
+    ln.wanted_jobs.clear();
+    return ln.wanted = B->pass_auto ? solo_kind(B, B->jobs.at(B->slot_job[slots[0]]).spec) : Kind::kSingles;
+  }
+  std::vector<std::pair<int, int>> jobs;
+  for (int slot : slots) jobs.push_back({slot, B->slot_job[slot]});
+  if (jobs == ln.wanted_jobs && ln.wanted_lanes == B->lanes.size()) return ln.wanted;
   bool pays[kNumStorage];
   passes_of(B, slots, pays);
-  return std::any_of(pays, pays + kNumStorage, [](bool p) { return p; }) ? Kind::kPasses : Kind::kSingles;
+  ln.wanted = std::any_of(pays, pays + kNumStorage, [](bool p) { return p; }) ? Kind::kPasses : Kind::kSingles;
+  ln.wanted_jobs = jobs;
+  ln.wanted_lanes = B->lanes.size();
+  return ln.wanted;
 }
 
 // Enqueue one chunk of the jobs in `slots` on a lane: the steps, then the
@@ -1800,7 +1813,7 @@ lbm_status lbm_batch_run_chunk(lbm_batch *B, int *n_active, int *n_queued) {
   // jobs of all of them would do so alike.
   const auto plan = plan_chunks(B);
   std::vector<Kind> kinds;
-  for (const auto &p : plan) kinds.push_back(B->lanes[p.first].wanted = wanted_kind(B, p.second));
+  for (const auto &p : plan) kinds.push_back(wanted_kind(B, B->lanes[p.first], p.second));
   for (const Lane &ln : B->lanes)
     if (ln.busy) kinds.push_back(ln.wanted);
   for (const auto &p : plan) {

@@ -1,6 +1,6 @@
-"""lbm_batch_autotune: a batch takes over the shape tuned for an earlier one only
-if it holds the same kind of work (storage forms and how they step, resident
-nodes to a power of two)."""
+"""What a batch makes of its jobs without being asked: the shape it tunes or takes
+over, the padding of rows, passes in shared chunks, grouped steps on lanes; the
+same bits each way."""
 import ctypes
 
 import pytest
