@@ -356,7 +356,10 @@ lbm_status lbm_get_launch(const lbm_lattice *L, int *block_x, int *nodes_per_thr
  * lattices (up to about 65000 nodes, without those options) make two or three
  * steps per launch and larger row-major ones make passes where they are
  * estimated to be faster -- with the same bits, in the buffer that single
- * steps end in.  Errors: LBM_ERR_ARG (NULL, steps_per_pass not 1 or 2,
+ * steps end in.  Such launches need whole compute units free at once: a
+ * program that runs several lattices on streams of their own, of very
+ * different sizes, keeps the small ones' pace by this call with 1 on each.
+ * Errors: LBM_ERR_ARG (NULL, steps_per_pass not 1 or 2,
  * z_planes < 0, tile_rows not 0, 5 or 12). */
 lbm_status lbm_set_steps_per_pass(lbm_lattice *L, int steps_per_pass, int z_planes, int tile_rows);
 lbm_status lbm_get_steps_per_pass(const lbm_lattice *L, int *steps_per_pass, int *z_planes, int *tile_rows);
@@ -550,7 +553,10 @@ lbm_status lbm_batch_get_shape(const lbm_batch *B, int *block_x, int *tile_nodes
  *                    of one job is grouped as lbm_step groups its steps, and
  *                    FP32 and FP64 jobs for which passes are estimated to be
  *                    faster make them in shared chunks too (those jobs are
- *                    stored row-major with padded rows);
+ *                    stored row-major with padded rows, where the budget has
+ *                    room for the padding) -- on several lanes at once only
+ *                    where all lanes' jobs would make launches of one kind,
+ *                    as those of different kinds hold one another up;
  *   2                every chunk by passes of two steps: one launch per
  *                    storage form over the 64 x 13 (FP64: 64 x 7) tiles and
  *                    z ranges of z_planes planes (0: 32) of all its jobs, or
